@@ -112,30 +112,45 @@ struct PermOut {
     float *means, *log_scales, *quats, *opacity, *sh;
 };
 
-__global__ __launch_bounds__(TR_THREADS) void k_permute(rgs_gaussians in, PermOut out, int nc,
-                                                        const int32_t* __restrict__ perm) {
+// Row-major: the grid's slow index is the row, so that the blocks in flight
+// gather from a row or two (64 MB each at 16M Gaussians), which the 256 MB
+// last-level cache holds, instead of from all 59 at once: each random 4-byte
+// read moves a line, mostly from that cache and not from HBM.  59 rows of a
+// random permutation: 22.8 -> 16.9 ms at 16M Gaussians, 1.00 -> 0.43 ms at 1M.
+static constexpr int PM_ITEMS = 4;
+
+__global__ __launch_bounds__(TR_THREADS) void k_permute(rgs_gaussians in, PermOut out, const int32_t* __restrict__ perm) {
     const int64_t n = in.n;
-    const int64_t j = (int64_t)blockIdx.x * TR_THREADS + threadIdx.x;
-    if (j >= n) return;
-    const int64_t s = perm[j];
-    if (s < 0 || s >= n) return;
+    const int r = blockIdx.y;
+    const float* src;
+    float* dst;
+    if (r < 3) { src = in.means + r * n; dst = out.means + r * n; }
+    else if (r < 6) { src = in.log_scales + (r - 3) * n; dst = out.log_scales + (r - 3) * n; }
+    else if (r < 10) { src = in.quats + (r - 6) * n; dst = out.quats + (r - 6) * n; }
+    else if (r == 10) { src = in.opacity; dst = out.opacity; }
+    else { src = in.sh + (r - 11) * n; dst = out.sh + (r - 11) * n; }
+    const int64_t base = (int64_t)blockIdx.x * (TR_THREADS * PM_ITEMS) + threadIdx.x;
+    int64_t s[PM_ITEMS];
+    float v[PM_ITEMS];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        out.means[a * n + j] = in.means[a * n + s];
-        out.log_scales[a * n + j] = in.log_scales[a * n + s];
+    for (int k = 0; k < PM_ITEMS; ++k) {
+        const int64_t j = base + k * TR_THREADS;
+        s[k] = j < n ? perm[j] : -1;
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) out.quats[a * n + j] = in.quats[a * n + s];
-    out.opacity[j] = in.opacity[s];
-    for (int k = 0; k < 3 * nc; ++k) out.sh[(int64_t)k * n + j] = in.sh[(int64_t)k * n + s];
+    for (int k = 0; k < PM_ITEMS; ++k) v[k] = (s[k] >= 0 && s[k] < n) ? src[s[k]] : 0.f;
+#pragma unroll
+    for (int k = 0; k < PM_ITEMS; ++k)
+        if (s[k] >= 0 && s[k] < n) dst[base + k * TR_THREADS] = v[k];
 }
 
 rgs_status permute_launch(const rgs_gaussians* in, const int32_t* perm, const rgs_gaussians_grad* out, hipStream_t s) {
     if (in->n <= 0) return RGS_OK;
-    const int nc = (in->sh_degree + 1) * (in->sh_degree + 1);
+    const int rows = 11 + 3 * (in->sh_degree + 1) * (in->sh_degree + 1);
     const PermOut o{out->means, out->log_scales, out->quats, out->opacity, out->sh};
-    hipLaunchKernelGGL(k_permute, dim3((unsigned)((in->n + TR_THREADS - 1) / TR_THREADS)), dim3(TR_THREADS), 0, s, *in, o,
-                       nc, perm);
+    const int64_t per = TR_THREADS * PM_ITEMS;
+    hipLaunchKernelGGL(k_permute, dim3((unsigned)((in->n + per - 1) / per), (unsigned)rows), dim3(TR_THREADS), 0, s, *in,
+                       o, perm);
     return launch_check();
 }
 
