@@ -23,9 +23,9 @@ size_t kd_ws_bytes(int64_t n, int L);
 rgs_status kd_partition(const rgs_gaussians* g, int L, float d_factor, int rule, const rgs_kdtree* kd, void* ws,
                         hipStream_t s);
 rgs_status project_launch(const rgs_gaussians* g, const ViewTable* vt, const float* split, const int32_t* center_cell,
-                          int cells, const uint32_t* own_mask, const rgs_projected* out, hipStream_t s);
+                          int cells, const uint32_t* own_mask, const rgs_projected* out, int n_views, hipStream_t s);
 rgs_status project_bwd_launch(const float* dproj, const rgs_gaussians* g, const uint32_t* count, const ViewTable* vt,
-                              const rgs_gaussians_grad* out, hipStream_t s);
+                              const rgs_gaussians_grad* out, int n_views, hipStream_t s);
 size_t bin_ws_bytes(int64_t n, int n_views, int64_t total_tiles, int L, int64_t capacity);
 size_t group_ws_bytes(int64_t n);
 rgs_status group_by_cell(const rgs_gaussians* in, const rgs_kdtree* kd, int L, const rgs_gaussians* out, int32_t* perm,
@@ -409,7 +409,7 @@ rgs_status rgs_project_sh(const rgs_gaussians* g, const rgs_camera* cams, int32_
     if (!disjoint(proj_spans(out, m), gauss_spans(g)) || !disjoint(proj_spans(out, m), {{views_dev, sizeof(ViewTable)}}))
         return RGS_E_ARG;
     return project_launch(g, reinterpret_cast<const ViewTable*>(views_dev), kd->split, kd->center_cell, cells,
-                          kd->own_mask, out, S(stream));
+                          kd->own_mask, out, n_views, S(stream));
 }
 
 size_t rgs_bin_sort_workspace(int64_t n, int32_t n_views, int64_t total_tiles, int32_t L, int64_t capacity) {
@@ -626,7 +626,7 @@ rgs_status rgs_project_sh_bwd(const float* d_proj, const rgs_gaussians* g, const
     if (!disjoint(grad_spans(out, g), concat(concat(gauss_spans(g), proj_spans(proj, m)),
                                              {{d_proj, 36 * m}, {views_dev, sizeof(ViewTable)}})))
         return RGS_E_ARG;
-    return project_bwd_launch(d_proj, g, proj->count, reinterpret_cast<const ViewTable*>(views_dev), out, S(stream));
+    return project_bwd_launch(d_proj, g, proj->count, reinterpret_cast<const ViewTable*>(views_dev), out, n_views, S(stream));
 }
 
 static bool grad_ptrs_ok(const rgs_gaussians_grad* g) {

@@ -283,51 +283,60 @@ __device__ __forceinline__ bool screen_may_hit(float mu0, float mu1, float mu2, 
 // leaves whose subset N_k holds the Gaussian (own_mask); RGS_CELLS_EXCLUSIVE,
 // the leaf of the centre only, with no indicator test in the render (flag
 // bit 0 set: the render takes every pixel of the footprint for that cell).
+//
+// A block of the sparse kernel takes PJ_IT * 256 consecutive Gaussians in two phases: the screen test
+// of each (cheap, coalesced), the survivors compacted in order in LDS, and
+// the fp64 chain and colours on full waves of survivors.  Where a few in a
+// hundred Gaussians reach the image (a city, an unsorted scene) nearly every
+// wave would otherwise run the whole chain for a lane or two.
+static constexpr int PJ_IT = 4;
+
+template <int IT>
+__device__ __forceinline__ int block_compact(const bool* keep, uint16_t* __restrict__ s_list, uint32_t* __restrict__ s_cnt) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint64_t b[IT];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        b[k] = __ballot(keep[k]);
+        if (lane == 0) s_cnt[k * 4 + w] = (uint32_t)__popcll(b[k]);
+    }
+    __syncthreads();
+    uint32_t run = 0;
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u == w && keep[k]) s_list[run + (uint32_t)__popcll(b[k] & lt_mask)] = (uint16_t)(k * PJ_THREADS + threadIdx.x);
+            run += s_cnt[k * 4 + u];
+        }
+    }
+    __syncthreads();
+    return (int)run;
+}
+
+// The projection of Gaussian i in the views of `scr` (their screen test passed).
+// z0 is 0, but the compiler does not know it: in the sparse kernel's loop over
+// survivors it keeps the camera constants' loads (and their fp64 copies) inside
+// the loop instead of in registers across it.
 template <int D>
-__global__ __launch_bounds__(PJ_THREADS, 3) void k_project(rgs_gaussians g, const ViewTable* __restrict__ vt,
-                                                        const float* __restrict__ split,
-                                                        const int32_t* __restrict__ center_cell, int cells,
-                                                        const uint32_t* __restrict__ own_mask, rgs_projected out) {
+__device__ __forceinline__ void project_kept(const rgs_gaussians& g, const ViewTable* __restrict__ vt, int z0,
+                                             const float* __restrict__ split, const int32_t* __restrict__ center_cell,
+                                             int cells, const uint32_t* __restrict__ own_mask, const rgs_projected& out,
+                                             int64_t i, uint32_t scr, float mu0, float mu1, float mu2, float ls0, float ls1,
+                                             float ls2) {
     const int64_t n = g.n;
-    const int64_t i = (int64_t)blockIdx.x * PJ_THREADS + threadIdx.x;
-    if (i >= n) return;
-    constexpr int nc = (D + 1) * (D + 1);
-    // cell culling: views that cannot see this Gaussian's cell get count 0,
-    // and the parameters are not read unless some view needs them
-    uint32_t view_ok = (1u << vt->n_views) - 1u;
-    if (vt->culled) {
-        const int cell = center_cell[i];
-        view_ok = 0u;
-        for (int v = 0; v < vt->n_views; ++v)
-            if ((vt->v[v].cell_visible >> cell) & 1ull) view_ok |= 1u << v;
-        for (int v = 0; v < vt->n_views; ++v)
-            if (!((view_ok >> v) & 1u)) out.count[(int64_t)v * n + i] = 0u;
-        if (view_ok == 0u) return;
-    }
-    const float mu0 = g.means[i], mu1 = g.means[n + i], mu2 = g.means[2 * n + i];
-    const float ls0 = g.log_scales[i], ls1 = g.log_scales[n + i], ls2 = g.log_scales[2 * n + i];
-    // pairs that cannot reach their image skip the fp64 chain (count 0, as the chain would give)
-    const float smax = expf(fmaxf(fmaxf(ls0, ls1), ls2)) * 1.001f;
-    uint32_t scr = 0u;  // views whose screen test passes
-    for (int v = 0; v < vt->n_views; ++v)
-        if (screen_may_hit(mu0, mu1, mu2, smax, vt->v[v])) scr |= 1u << v;
-    if ((view_ok & scr) == 0u) {
-        for (int v = 0; v < vt->n_views; ++v)
-            if ((view_ok >> v) & 1u) out.count[(int64_t)v * n + i] = 0u;
-        return;
-    }
     const float qw = g.quats[i], qx = g.quats[n + i], qy = g.quats[2 * n + i], qz = g.quats[3 * n + i];
     const float logit = g.opacity[i];
     Pre32 pre;
     pre32(ls0, ls1, ls2, qw, qx, qy, qz, logit, pre);
     const int L = vt->L;
     for (int v = 0; v < vt->n_views; ++v) {
-        if (!((view_ok >> v) & 1u)) continue;
-        const ViewParams& V = vt->v[v];
+        if (!((scr >> v) & 1u)) continue;
+        const ViewParams& V = vt->v[v + z0];
         const int64_t src = (int64_t)v * n + i;
         Proj32 p;
-        p.vis = false;
-        if ((scr >> v) & 1u) proj32(mu0, mu1, mu2, pre, V, p);
+        proj32(mu0, mu1, mu2, pre, V, p);
         int r[4] = {0, 0, 0, 0};
         bool ok = p.vis && rect32(p, V, r);
         float4* rec = reinterpret_cast<float4*>(out.rec + src * RGS_REC_FLOATS);
@@ -384,15 +393,23 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project(rgs_gaussians g, cons
         // Gaussian read them; a later view hits the cache), not held in
         // registers across the view loop, so that more waves fit per SIMD
         float col[3] = {0.5f, 0.5f, 0.5f};
+        constexpr int BAND = 3 * (2 * D + 1);
 #pragma unroll
         for (int l = 0; l <= D; ++l) {
-            // one band at a time: the empty asm keeps the compiler from
-            // hoisting every band's loads (and their registers) up front
-            asm volatile("" ::: "memory");
+            // one band at a time: the empty asm ties the band's addresses to
+            // the colour so far, so that its loads (and their registers) are
+            // not hoisted above the band before; the scheduling barrier has
+            // all of them issued before the first is waited for
+            int64_t il = i;
+            asm volatile("" : "+v"(il), "+v"(col[0]), "+v"(col[1]), "+v"(col[2]));
+            float f[BAND];
 #pragma unroll
-            for (int j = l * l; j < (l + 1) * (l + 1); ++j)
+            for (int j = 0; j < 3 * (2 * l + 1); ++j) f[j] = g.sh[(int64_t)(3 * l * l + j) * n + il];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int ch = 0; ch < 3; ++ch) col[ch] = fmaf(g.sh[(int64_t)(3 * j + ch) * n + i], Y[j], col[ch]);
+            for (int j = 0; j < 2 * l + 1; ++j)
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) col[ch] = fmaf(f[3 * j + ch], Y[l * l + j], col[ch]);
         }
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) col[ch] = fmaxf(col[ch], 0.0f);
@@ -407,19 +424,140 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project(rgs_gaussians g, cons
     }
 }
 
+// Views whose image Gaussian (mu, ls) can reach, of those in view_ok.
+__device__ __forceinline__ uint32_t screen_views(const ViewTable* __restrict__ vt, uint32_t view_ok, const float mu[3],
+                                                 const float ls[3]) {
+    const float smax = expf(fmaxf(fmaxf(ls[0], ls[1]), ls[2])) * 1.001f;
+    uint32_t scr = 0u;
+    for (int v = 0; v < vt->n_views; ++v)
+        if (((view_ok >> v) & 1u) && screen_may_hit(mu[0], mu[1], mu[2], smax, vt->v[v])) scr |= 1u << v;
+    return scr;
+}
+
+// Views that can see a cell (cell culling: the others get count 0, and the
+// parameters are not read unless some view needs them).
+__device__ __forceinline__ uint32_t cell_views(const ViewTable* __restrict__ vt, int cell) {
+    uint32_t ok = 0u;
+    for (int v = 0; v < vt->n_views; ++v)
+        if ((vt->v[v].cell_visible >> cell) & 1ull) ok |= 1u << v;
+    return ok;
+}
+
+template <int D>
+__global__ __launch_bounds__(PJ_THREADS, 3) void k_project(rgs_gaussians g, const ViewTable* __restrict__ vt,
+                                                        const float* __restrict__ split,
+                                                        const int32_t* __restrict__ center_cell, int cells,
+                                                        const uint32_t* __restrict__ own_mask, rgs_projected out) {
+    const int64_t n = g.n;
+    const int64_t i = (int64_t)blockIdx.x * PJ_THREADS + threadIdx.x;
+    if (i >= n) return;
+    uint32_t scr = vt->culled ? cell_views(vt, center_cell[i]) : (1u << vt->n_views) - 1u;
+    float mu[3] = {0.f, 0.f, 0.f}, ls[3] = {0.f, 0.f, 0.f};
+    if (scr) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            mu[a] = g.means[a * n + i];
+            ls[a] = g.log_scales[a * n + i];
+        }
+        // pairs that cannot reach their image skip the fp64 chain (count 0, as the chain would give)
+        scr = screen_views(vt, scr, mu, ls);
+    }
+    for (int v = 0; v < vt->n_views; ++v)
+        if (!((scr >> v) & 1u)) out.count[(int64_t)v * n + i] = 0u;
+    if (scr == 0u) return;
+    project_kept<D>(g, vt, 0, split, center_cell, cells, own_mask, out, i, scr, mu[0], mu[1], mu[2], ls[0], ls[1], ls[2]);
+}
+
+template <int D>
+__global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians g, const ViewTable* __restrict__ vt,
+                                                        const float* __restrict__ split,
+                                                        const int32_t* __restrict__ center_cell, int cells,
+                                                        const uint32_t* __restrict__ own_mask, rgs_projected out) {
+    __shared__ uint16_t s_list[PJ_IT * PJ_THREADS];
+    __shared__ uint16_t s_views[PJ_IT * PJ_THREADS];  // views whose screen test passes
+    __shared__ uint32_t s_cnt[PJ_IT * 4];
+    const int64_t n = g.n;
+    const int64_t base = (int64_t)blockIdx.x * (PJ_IT * PJ_THREADS);
+    bool keep[PJ_IT];
+    {
+        uint32_t view_ok[PJ_IT];
+#pragma unroll
+        for (int k = 0; k < PJ_IT; ++k) view_ok[k] = (1u << vt->n_views) - 1u;
+        if (vt->culled) {
+            int cell[PJ_IT];
+#pragma unroll
+            for (int k = 0; k < PJ_IT; ++k) {
+                const int64_t i = base + k * PJ_THREADS + threadIdx.x;
+                cell[k] = center_cell[i < n ? i : n - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < PJ_IT; ++k) view_ok[k] = cell_views(vt, cell[k]);
+        }
+        // all loads of the thread before their use
+        float mu[PJ_IT][3], ls[PJ_IT][3];
+#pragma unroll
+        for (int k = 0; k < PJ_IT; ++k) {
+            const int64_t i = base + k * PJ_THREADS + threadIdx.x;
+            if (i >= n) view_ok[k] = 0u;
+            if (view_ok[k] == 0u) continue;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                mu[k][a] = g.means[a * n + i];
+                ls[k][a] = g.log_scales[a * n + i];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PJ_IT; ++k) {
+            const int64_t i = base + k * PJ_THREADS + threadIdx.x;
+            keep[k] = false;
+            if (i >= n) continue;
+            const uint32_t scr = view_ok[k] ? screen_views(vt, view_ok[k], mu[k], ls[k]) : 0u;
+            for (int v = 0; v < vt->n_views; ++v)
+                if (!((scr >> v) & 1u)) out.count[(int64_t)v * n + i] = 0u;
+            keep[k] = scr != 0u;
+            s_views[k * PJ_THREADS + threadIdx.x] = (uint16_t)scr;
+        }
+    }
+    const int m = block_compact<PJ_IT>(keep, s_list, s_cnt);
+#pragma unroll 1
+    for (int q = threadIdx.x; q < m; q += PJ_THREADS) {
+        int z0 = 0;
+        asm volatile("" : "+s"(z0));
+        const int loc = s_list[q];
+        const int64_t i = base + loc;
+        project_kept<D>(g, vt, z0, split, center_cell, cells, own_mask, out, i, s_views[loc], g.means[i], g.means[n + i],
+                        g.means[2 * n + i], g.log_scales[i], g.log_scales[n + i], g.log_scales[2 * n + i]);
+    }
+}
+
+// The sparse kernels are taken for large scenes seen by one or two views, where
+// most Gaussians are outside the image (16M-Gaussian city, one 4K view:
+// projection 0.73 -> 0.39 ms, geometric backward 0.61 -> 0.33, SH backward 1.23
+// -> 0.81).  Where most are kept the direct ones are faster: 1M Gaussians, 91%
+// visible: 93 against 117 us, 48 against 56, 77 against 83; so they stay for
+// smaller scenes, and for more views of one scene, which together keep nearly
+// all of it (4M Gaussians, 16 views: geometric backward 1.13 against 1.35 ms).
+static bool few_kept(int64_t n, int n_views) { return n >= 2000000 && n_views <= 2; }
+
+template <int D>
+static void project_one(const rgs_gaussians* g, const ViewTable* vt, const float* split, const int32_t* center_cell, int cells,
+                        const uint32_t* own_mask, const rgs_projected* out, int n_views, hipStream_t s) {
+    if (few_kept(g->n, n_views))
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project_sparse<D>), dim3((unsigned)((g->n + PJ_IT * PJ_THREADS - 1) / (PJ_IT * PJ_THREADS))),
+                           dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells, own_mask, *out);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project<D>), dim3((unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS)),
+                           dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells, own_mask, *out);
+}
+
 rgs_status project_launch(const rgs_gaussians* g, const ViewTable* vt, const float* split, const int32_t* center_cell,
-                          int cells, const uint32_t* own_mask, const rgs_projected* out, hipStream_t s) {
+                          int cells, const uint32_t* own_mask, const rgs_projected* out, int n_views, hipStream_t s) {
     if (g->n <= 0) return RGS_OK;
-    const unsigned grid = (unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS);
     switch (g->sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project<0>, dim3(grid), dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells,
-                                   own_mask, *out); break;
-        case 1: hipLaunchKernelGGL(k_project<1>, dim3(grid), dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells,
-                                   own_mask, *out); break;
-        case 2: hipLaunchKernelGGL(k_project<2>, dim3(grid), dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells,
-                                   own_mask, *out); break;
-        default: hipLaunchKernelGGL(k_project<3>, dim3(grid), dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells,
-                                    own_mask, *out); break;
+        case 0: project_one<0>(g, vt, split, center_cell, cells, own_mask, out, n_views, s); break;
+        case 1: project_one<1>(g, vt, split, center_cell, cells, own_mask, out, n_views, s); break;
+        case 2: project_one<2>(g, vt, split, center_cell, cells, own_mask, out, n_views, s); break;
+        default: project_one<3>(g, vt, split, center_cell, cells, own_mask, out, n_views, s); break;
     }
     return launch_check();
 }
@@ -434,13 +572,15 @@ rgs_status project_launch(const rgs_gaussians* g, const ViewTable* vt, const flo
 // proportion to s00 s11 / det in fp32; the SH colour part (fp32) runs after
 // it and adds its share of the mean gradient (the view direction).  Split,
 // each kernel keeps fewer registers live than one kernel doing both.
-__global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo(const float* __restrict__ dproj, rgs_gaussians g,
-                                                                const uint32_t* __restrict__ count,
-                                                                const ViewTable* __restrict__ vt,
-                                                                rgs_gaussians_grad out) {
+//
+// Its sparse form takes PJ_IT * 256 Gaussians per block as the projection's
+// does: zeros for those that no view keeps, without reading a parameter, and
+// the adjoint on full waves of the others.
+// (z0 as in project_kept.)
+__device__ __forceinline__ void geo_kept(const float* __restrict__ dproj, const rgs_gaussians& g,
+                                         const uint32_t* __restrict__ count, const ViewTable* __restrict__ vt, int z0,
+                                         const rgs_gaussians_grad& out, int64_t i) {
     const int64_t n = g.n;
-    const int64_t i = (int64_t)blockIdx.x * PJ_THREADS + threadIdx.x;
-    if (i >= n) return;
     const int64_t VN = (int64_t)vt->n_views * n;
     const double mu[3] = {g.means[i], g.means[n + i], g.means[2 * n + i]};
     const float ls[3] = {g.log_scales[i], g.log_scales[n + i], g.log_scales[2 * n + i]};
@@ -463,13 +603,11 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo(const float* __r
             S[a][b] = ((Rq[a][0] * s[0]) * (Rq[b][0] * s[0]) + (Rq[a][1] * s[1]) * (Rq[b][1] * s[1])) +
                       (Rq[a][2] * s[2]) * (Rq[b][2] * s[2]);
     double GS[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-    bool any = false;
 
     for (int v = 0; v < vt->n_views; ++v) {
         const int64_t src = (int64_t)v * n + i;
         if (count[src] == 0u) continue;
-        any = true;
-        const ViewParams& V = vt->v[v];
+        const ViewParams& V = vt->v[v + z0];
         float gd[6];
         for (int c = 0; c < 6; ++c) gd[c] = dproj[c * VN + src];
         double R[9];
@@ -537,7 +675,7 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo(const float* __r
         gop += gd[5] * alpha * (1.f - alpha);
     }
     double gls[3] = {0.0, 0.0, 0.0}, gq[4] = {0.0, 0.0, 0.0, 0.0};
-    if (any) {
+    {
         // S = M M^T with M = Rq diag(s): G_M = 2 G_S M
         double GR[3][3];
         for (int b = 0; b < 3; ++b) {
@@ -569,9 +707,59 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo(const float* __r
     out.opacity[i] = gop;
 }
 
+__device__ __forceinline__ void geo_zero(const rgs_gaussians_grad& out, int64_t n, int64_t i) {
+    for (int a = 0; a < 3; ++a) { out.means[a * n + i] = 0.f; out.log_scales[a * n + i] = 0.f; }
+    for (int a = 0; a < 4; ++a) out.quats[a * n + i] = 0.f;
+    out.opacity[i] = 0.f;
+}
+
+__global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo(const float* __restrict__ dproj, rgs_gaussians g,
+                                                                const uint32_t* __restrict__ count,
+                                                                const ViewTable* __restrict__ vt,
+                                                                rgs_gaussians_grad out) {
+    const int64_t i = (int64_t)blockIdx.x * PJ_THREADS + threadIdx.x;
+    if (i >= g.n) return;
+    bool any = false;
+    for (int v = 0; v < vt->n_views; ++v) any = any || count[(int64_t)v * g.n + i] != 0u;
+    if (any) geo_kept(dproj, g, count, vt, 0, out, i);
+    else geo_zero(out, g.n, i);
+}
+
+__global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo_sparse(const float* __restrict__ dproj, rgs_gaussians g,
+                                                                       const uint32_t* __restrict__ count,
+                                                                       const ViewTable* __restrict__ vt,
+                                                                       rgs_gaussians_grad out) {
+    __shared__ uint16_t s_list[PJ_IT * PJ_THREADS];
+    __shared__ uint32_t s_cnt[PJ_IT * 4];
+    const int64_t n = g.n;
+    const int64_t base = (int64_t)blockIdx.x * (PJ_IT * PJ_THREADS);
+    bool keep[PJ_IT];
+#pragma unroll
+    for (int k = 0; k < PJ_IT; ++k) keep[k] = false;
+    for (int v = 0; v < vt->n_views; ++v) {
+#pragma unroll
+        for (int k = 0; k < PJ_IT; ++k) {
+            const int64_t i = base + k * PJ_THREADS + threadIdx.x;
+            if (i < n && count[(int64_t)v * n + i] != 0u) keep[k] = true;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PJ_IT; ++k) {
+        const int64_t i = base + k * PJ_THREADS + threadIdx.x;
+        if (i < n && !keep[k]) geo_zero(out, n, i);
+    }
+    const int m = block_compact<PJ_IT>(keep, s_list, s_cnt);
+#pragma unroll 1
+    for (int q = threadIdx.x; q < m; q += PJ_THREADS) {
+        int z0 = 0;
+        asm volatile("" : "+s"(z0));
+        geo_kept(dproj, g, count, vt, z0, out, base + s_list[q]);
+    }
+}
+
 // SH colour part: gradients of the SH coefficients, and the view-direction
 // share of the mean gradient added to what the geometric kernel wrote.
-template <int D>
+template <int D, bool FEW>
 __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_sh(const float* __restrict__ dproj, rgs_gaussians g,
                                                                const uint32_t* __restrict__ count,
                                                                const ViewTable* __restrict__ vt,
@@ -581,19 +769,26 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_sh(const float* __re
     if (i >= n) return;
     constexpr int nc = (D + 1) * (D + 1);
     const int64_t VN = (int64_t)vt->n_views * n;
-    const float mu[3] = {g.means[i], g.means[n + i], g.means[2 * n + i]};
+    // FEW: a Gaussian that no view keeps gets zeros without its coefficients
+    // being read; else the coefficients are loaded before the counts are known
+    bool any = false;
+    if (FEW)
+        for (int v = 0; v < vt->n_views; ++v) any = any || count[(int64_t)v * n + i] != 0u;
+    float mu[3] = {0.f, 0.f, 0.f};
     float gmu[3] = {0.f, 0.f, 0.f};
     float gsh[3 * nc], fsh[3 * nc];
 #pragma unroll
-    for (int k = 0; k < 3 * nc; ++k) {
-        gsh[k] = 0.f;
-        fsh[k] = g.sh[(int64_t)k * n + i];
+    for (int k = 0; k < 3 * nc; ++k) gsh[k] = fsh[k] = 0.f;
+    if (!FEW || any) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) mu[a] = g.means[a * n + i];
+#pragma unroll
+        for (int k = 0; k < 3 * nc; ++k) fsh[k] = g.sh[(int64_t)k * n + i];
     }
-    bool any = false;
     for (int v = 0; v < vt->n_views; ++v) {
         const int64_t src = (int64_t)v * n + i;
-        if (count[src] == 0u) continue;
-        any = true;
+        if ((FEW && !any) || count[src] == 0u) continue;
+        if (!FEW) any = true;
         const ViewParams& V = vt->v[v];
         const float gd6 = dproj[6 * VN + src], gd7 = dproj[7 * VN + src], gd8 = dproj[8 * VN + src];
         float d[3] = {mu[0] - V.o[0], mu[1] - V.o[1], mu[2] - V.o[2]};
@@ -630,16 +825,33 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_sh(const float* __re
     for (int k = 0; k < 3 * nc; ++k) out.sh[(int64_t)k * n + i] = gsh[k];
 }
 
+template <int D>
+static void project_bwd_sh_one(const float* dproj, const rgs_gaussians* g, const uint32_t* count, const ViewTable* vt,
+                               const rgs_gaussians_grad* out, bool few, hipStream_t s) {
+    const dim3 grid((unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS));
+    if (few)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project_bwd_sh<D, true>), grid, dim3(PJ_THREADS), 0, s, dproj, *g, count, vt, *out);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project_bwd_sh<D, false>), grid, dim3(PJ_THREADS), 0, s, dproj, *g, count, vt,
+                           *out);
+}
+
 rgs_status project_bwd_launch(const float* dproj, const rgs_gaussians* g, const uint32_t* count, const ViewTable* vt,
-                              const rgs_gaussians_grad* out, hipStream_t s) {
+                              const rgs_gaussians_grad* out, int n_views, hipStream_t s) {
     if (g->n <= 0) return RGS_OK;
     const unsigned grid = (unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS);
-    hipLaunchKernelGGL(k_project_bwd_geo, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt, *out);
+    const bool few = few_kept(g->n, n_views);
+    if (few)
+        hipLaunchKernelGGL(k_project_bwd_geo_sparse, dim3((grid + PJ_IT - 1) / PJ_IT), dim3(PJ_THREADS), 0, s, dproj, *g,
+                           count, vt, *out);
+    else
+        hipLaunchKernelGGL(k_project_bwd_geo, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt,
+                           *out);
     switch (g->sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_bwd_sh<0>, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt, *out); break;
-        case 1: hipLaunchKernelGGL(k_project_bwd_sh<1>, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt, *out); break;
-        case 2: hipLaunchKernelGGL(k_project_bwd_sh<2>, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt, *out); break;
-        default: hipLaunchKernelGGL(k_project_bwd_sh<3>, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt, *out); break;
+        case 0: project_bwd_sh_one<0>(dproj, g, count, vt, out, few, s); break;
+        case 1: project_bwd_sh_one<1>(dproj, g, count, vt, out, few, s); break;
+        case 2: project_bwd_sh_one<2>(dproj, g, count, vt, out, few, s); break;
+        default: project_bwd_sh_one<3>(dproj, g, count, vt, out, few, s); break;
     }
     return launch_check();
 }
