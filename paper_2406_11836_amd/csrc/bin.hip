@@ -131,7 +131,7 @@ __global__ __launch_bounds__(BN_THREADS) void k_pair_counts(const uint32_t* __re
                                                             const uint32_t* __restrict__ count,
                                                             int32_t* __restrict__ pair_rank, uint32_t* __restrict__ cnt,
                                                             uint32_t* __restrict__ tsum, uint32_t* __restrict__ fill,
-                                                            int64_t n_fill) {
+                                                            int64_t n_fill, uint32_t* __restrict__ zero, int n_zero) {
     __shared__ uint32_t s_w[BN_THREADS / 64];
     const int64_t np = (int64_t)*n_dev;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -165,6 +165,8 @@ __global__ __launch_bounds__(BN_THREADS) void k_pair_counts(const uint32_t* __re
     // the slot table's empty marks, needed after the instance sort
     for (int64_t i = (int64_t)blockIdx.x * BN_THREADS + threadIdx.x; i < n_fill; i += (int64_t)gridDim.x * BN_THREADS)
         fill[i] = 0xffffffffu;
+    // the instance sort's digit counts, which a few blocks' emission adds to
+    for (int i = blockIdx.x * BN_THREADS + threadIdx.x; i < n_zero; i += gridDim.x * BN_THREADS) zero[i] = 0u;
 }
 
 // Position of the c-th set bit (0-based) of a 64-bit mask.
@@ -185,162 +187,214 @@ __device__ __forceinline__ uint32_t udiv_small(uint32_t a, uint32_t b) {
     return q;
 }
 
-// Instance emission, balanced over instances: a block takes 256 consecutive
-// ordered pairs, stages their offsets in LDS and walks the block's instances
-// in chunks of 256; each thread finds its pair by binary search and decodes
-// (cell, tile) from the index inside the pair (cells ascending, then the row
-// spans' tiles top to bottom, left to right), so writes are coalesced
-// whatever the per-pair counts.  Small rectangles carry their spans in the
-// record's descriptor.  For larger ones the block computes each row's span
-// once, rows spread over the threads, into an LDS pool with per-pair running
-// sums, and an instance finds its row by binary search; when a chunk's large
-// rectangles hold more rows than the pool, the chunk is taken in runs of
-// consecutive pairs whose rows fit.
-__global__ __launch_bounds__(BN_THREADS) void k_emit(const uint32_t* __restrict__ pair_src, const uint32_t* __restrict__ n_dev,
-                                                     const uint32_t* __restrict__ pair_off, const float* __restrict__ rec,
-                                                     const uint32_t* __restrict__ bin, int64_t n_gauss,
-                                                     const ViewTable* __restrict__ vt, uint32_t* __restrict__ keys,
-                                                     uint64_t* __restrict__ vals) {
-    constexpr int ROWPOOL = 2048;  // rows of one run; a rectangle has at most 256 tile rows
-    __shared__ uint32_t s_off[BN_THREADS + 1];
-    __shared__ uint32_t s_src[BN_THREADS];
-    __shared__ uint64_t s_mask[BN_THREADS];
-    __shared__ uint64_t s_desc[BN_THREADS];  // row-span descriptor, or RGS_NO_SPANS
-    __shared__ uint2 s_rect[BN_THREADS];     // packed rectangle of the record
-    // per pair: tiles per cell, the view's first global tile and tiles per row
-    __shared__ uint32_t s_nt[BN_THREADS], s_vto[BN_THREADS], s_vtx[BN_THREADS];
-    __shared__ uint8_t s_view[BN_THREADS];
-    __shared__ uint32_t s_rows[BN_THREADS], s_rend[BN_THREADS];  // pooled rows per pair, inclusive scan
+// Instance emission, balanced over instances: a block takes a range of
+// consecutive instances, whatever pairs they belong to, and writes their keys,
+// sources and the sort's first digit counts.  (A block per 256 pairs left the
+// nearest pairs of a close-up, thousands of tiles each, to one block: a 16M city
+// at 4K took 1.97 ms, now 0.10; 1M clustered Gaussians 49 us and 9 for the
+// histogram pass, now 54 with it.)  The range is a tile of the sort, block after
+// block in its units; a sort of few tiles (FOLD) takes 256 instances per block,
+// for enough blocks, and adds the counts to the table, which k_pair_counts
+// cleared.  The pair holding a range's first instance comes from the offsets
+// scan; pairs are staged PC at a time (binning records, one 32-byte line each),
+// and an instance finds its pair by binary search in LDS and decodes (cell,
+// tile) from its index inside the pair (cells ascending, then the row spans'
+// tiles top to bottom, left to right), so writes are coalesced whatever the
+// per-pair counts.  Small rectangles carry their spans in the record's
+// descriptor.  For larger ones the block computes each row's span once, rows
+// spread over the threads, into an LDS pool with per-pair running sums, and an
+// instance finds its row by binary search; when a chunk's large rectangles hold
+// more rows than the pool, the chunk is taken in runs of consecutive pairs
+// whose rows fit.
+template <int BITS, bool FOLD>
+__global__ __launch_bounds__(BN_THREADS) void k_emit(const uint32_t* __restrict__ pair_src, const uint32_t* __restrict__ cnt,
+                                                     const uint32_t* __restrict__ pair_off,
+                                                     const uint32_t* __restrict__ first, const float* __restrict__ rec,
+                                                     const uint32_t* __restrict__ bin, uint32_t n_gauss,
+                                                     const ViewTable* __restrict__ vt, int items, uint32_t* __restrict__ ws_a,
+                                                     uint32_t* __restrict__ ws_b, uint32_t* __restrict__ keys,
+                                                     uint32_t* __restrict__ srcs) {
+    constexpr int NB = 1 << BITS;
+    constexpr int GROUP = FOLD ? RGS_FIRST_GROUP : RGS_RADIX_TILE;  // instances per range
+    constexpr int PC = BN_THREADS;  // pairs staged at a time (512: 36 instead of 25 KB of LDS, 64 against 54 us)
+    constexpr int ROWPOOL = 2048;  // rows of one run; a rectangle has at most 2048 tile rows
+    __shared__ uint32_t s_off[PC + 1];
+    __shared__ uint32_t s_src[PC];
+    __shared__ uint4 s_r0[PC], s_r1[PC];  // the binning record: rectangle, row-span descriptor | cell mask, count, tiles per cell
+    __shared__ uint8_t s_view[PC];
+    __shared__ uint16_t s_rows[PC];  // pooled rows per pair
+    __shared__ uint32_t s_rend[PC];  // ... and their inclusive scan
     __shared__ uint32_t s_rcum[ROWPOOL];  // a row's tile count, then the pair's running sum
     __shared__ int16_t s_rc0[ROWPOOL];    // the row's first tile column
     __shared__ uint32_t s_wsum[BN_THREADS / 64];
-    const int64_t npairs = (int64_t)*n_dev;
-    const int L = vt->L;
+    __shared__ uint32_t s_h[NB];
+    __shared__ uint32_t s_vto[RGS_MAX_VIEWS], s_vtx[RGS_MAX_VIEWS];  // a view's first global tile, its tiles per row
+    const uint32_t npairs = cnt[0];
+    const int64_t ninst = (int64_t)cnt[1];
+    const int L = vt->L, nv = vt->n_views;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    for (int64_t r0 = (int64_t)blockIdx.x * BN_THREADS; r0 < npairs; r0 += (int64_t)gridDim.x * BN_THREADS) {
-        const int nb = (int)((npairs - r0) < BN_THREADS ? (npairs - r0) : BN_THREADS);
-        uint32_t rows = 0;
-        if (t < nb) {
-            const uint32_t src = pair_src[r0 + t];
-            // the pair's binning record: one 32-byte line
-            const uint4* bp = reinterpret_cast<const uint4*>(bin) + 2 * (size_t)src;
-            const uint4 b0 = bp[0], b1 = bp[1];
-            const int v = (int)(src / (uint64_t)n_gauss);  // once per pair
-            const ViewParams& V = vt->v[v];
-            const uint64_t desc = (uint64_t)b0.z | ((uint64_t)b0.w << 32);
-            const uint32_t ry = b0.y;
-            s_src[t] = src;
-            s_mask[t] = (uint64_t)b1.x | ((uint64_t)b1.y << 32);
-            s_nt[t] = b1.w;
-            s_rect[t] = make_uint2(b0.x, ry);
-            s_desc[t] = desc;
-            s_off[t] = pair_off[r0 + t];
-            s_vto[t] = V.tile_offset;
-            s_vtx[t] = (uint32_t)V.tiles_x;
-            s_view[t] = (uint8_t)v;
-            if (desc == RGS_NO_SPANS)
-                rows = (uint32_t)(((int)(int16_t)(ry >> 16) >> 4) - ((int)(int16_t)(ry & 0xffffu) >> 4) + 1);
-        }
-        s_rows[t] = rows;
-        if (t == 0) s_off[nb] = pair_off[r0 + nb];
-        if (t > nb) s_off[t] = 0xffffffffu;  // past the chunk: above every instance index
-        {  // inclusive scan of the pooled rows over the chunk's pairs
-            const uint32_t inc = wave_incl_scan(rows);
-            if (lane == 63) s_wsum[w] = inc;
-            __syncthreads();
-            uint32_t before = 0;
-            for (int k = 0; k < w; ++k) before += s_wsum[k];
-            s_rend[t] = before + inc;
-        }
-        __syncthreads();
-        for (int p0 = 0; p0 < nb;) {
-            // the longest run of pairs from p0 whose pooled rows fit (at least p0 itself)
-            const uint32_t rbase = p0 > 0 ? s_rend[p0 - 1] : 0u;
-            int lo = p0 + 1, hi = nb;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_rend[mid - 1] - rbase <= (uint32_t)ROWPOOL) lo = mid; else hi = mid - 1;
-            }
-            const int p1 = lo;
-            const uint32_t nrows = s_rend[p1 - 1] - rbase;
-            // spans of the run's pooled rows, one row per thread
-            for (uint32_t r = t; r < nrows; r += BN_THREADS) {
-                const uint32_t g = rbase + r;
-                int a = p0, b = p1 - 1;  // owner: the first pair whose scan end exceeds g
-                while (a < b) {
-                    const int mid = (a + b) >> 1;
-                    if (s_rend[mid] > g) b = mid; else a = mid + 1;
-                }
-                const float4* rp = reinterpret_cast<const float4*>(rec + (size_t)s_src[a] * RGS_REC_FLOATS);
-                const float4 ra = rp[0], rb = rp[1];
-                SpanPre sp;
-                span_pre(ra.x, ra.y, ra.z, ra.w, rb.x, rb.z, sp);
-                const uint2 rr = s_rect[a];
-                const int x_lo = (int)(int16_t)(rr.x & 0xffffu), x_hi = (int)(int16_t)(rr.x >> 16);
-                const int y_lo = (int)(int16_t)(rr.y & 0xffffu), y_hi = (int)(int16_t)(rr.y >> 16);
-                const int row = (int)(g - (s_rend[a] - s_rows[a]));
-                const int2 cs = row_span(sp, x_lo, x_hi, y_lo, y_hi, (y_lo >> 4) + row);
-                s_rcum[r] = cs.x <= cs.y ? (uint32_t)(cs.y - cs.x + 1) : 0u;
-                s_rc0[r] = (int16_t)cs.x;
-            }
-            __syncthreads();
-            if (t >= p0 && t < p1 && s_rows[t] > 0u) {  // running sums per pooled pair
-                const uint32_t b0 = s_rend[t] - s_rows[t] - rbase;
-                uint32_t run = 0;
-                for (uint32_t r = 0; r < s_rows[t]; ++r) {
-                    run += s_rcum[b0 + r];
-                    s_rcum[b0 + r] = run;
-                }
-            }
-            __syncthreads();
-            const uint32_t j0 = s_off[p0], j1 = s_off[p1];
-            for (uint32_t j = j0 + t; j < j1; j += BN_THREADS) {
-                // last pair with s_off[p] <= j (offsets increase; entries past nb are ~0)
-                int pl = 0;
-#pragma unroll
-                for (int step = BN_THREADS / 2; step > 0; step >>= 1)
-                    if (s_off[pl + step] <= j) pl += step;
-                const uint32_t nt = s_nt[pl];
-                const uint32_t q = j - s_off[pl];
-                const uint32_t c = udiv_small(q, nt);
-                const uint32_t tt = q - c * nt;  // index among the pair's tiles, rows top to bottom
-                const uint2 rr = s_rect[pl];
-                const int tx0 = (int)(int16_t)(rr.x & 0xffffu) >> 4;
-                const int ty0 = (int)(int16_t)(rr.y & 0xffffu) >> 4;
-                int tx, ty;
-                const uint64_t desc = s_desc[pl];
-                if (desc != RGS_NO_SPANS) {
-                    // row of tile tt by byte-wise prefix sums of the 8 row lengths
-                    // (each < 16, total < 128): byte k of `pre` = tiles in rows 0..k,
-                    // and the high bit of byte k of `ge` is set iff pre_k > tt
-                    constexpr uint64_t ONES = 0x0101010101010101ull, HIGH = 0x8080808080808080ull;
-                    const uint64_t lens = (desc >> 4) & 0x0f0f0f0f0f0f0f0full;
-                    const uint64_t pre = lens * ONES;
-                    const uint64_t ge = ((pre | HIGH) - (uint64_t)(tt + 1u) * ONES) & HIGH;
-                    const int k = ge ? (__builtin_ctzll(ge) >> 3) : 7;
-                    const uint32_t before = ((uint32_t)(pre >> (8 * k)) & 0xffu) - ((uint32_t)(lens >> (8 * k)) & 0xffu);
-                    tx = tx0 + (int)((uint32_t)(desc >> (8 * k)) & 15u) + (int)(tt - before);
-                    ty = ty0 + k;
-                } else {
-                    // pooled rows: the first row whose running sum exceeds tt
-                    const uint32_t b0 = s_rend[pl] - s_rows[pl] - rbase;
-                    int a = 0, b = (int)s_rows[pl] - 1;
-                    while (a < b) {
-                        const int mid = (a + b) >> 1;
-                        if (s_rcum[b0 + mid] > tt) b = mid; else a = mid + 1;
+    if (t < nv) {
+        s_vto[t] = vt->v[t].tile_offset;
+        s_vtx[t] = (uint32_t)vt->v[t].tiles_x;
+    }
+    const RadixTab tab = radix_tab(ninst, items, FOLD ? 1 : 0, ws_a, ws_b);
+    const int units = FOLD ? (int)((ninst + GROUP - 1) / GROUP) : tab.units, per = FOLD ? 1 : tab.per;
+    for (int unit = blockIdx.x; unit < units; unit += gridDim.x) {
+        uint32_t dsum = 0;  // digit t's count in the unit
+        for (int u = 0; u < per; ++u) {
+            const int range = unit * per + u;
+            const int64_t j00 = (int64_t)range * GROUP;
+            if (j00 >= ninst) break;  // uniform
+            const uint32_t J0 = (uint32_t)j00, J1 = (uint32_t)(j00 + GROUP < ninst ? j00 + GROUP : ninst);
+            if (t < NB) s_h[t] = 0u;
+            for (uint32_t r0 = first[range]; r0 < npairs; r0 += PC) {
+                const int nb = (int)(npairs - r0 < (uint32_t)PC ? npairs - r0 : (uint32_t)PC);
+                bool large = false;
+                {
+                    const int p = t;
+                    uint32_t rows = 0;
+                    if (p < nb) {
+                        const uint32_t off = pair_off[r0 + p], src = pair_src[r0 + p];
+                        s_off[p] = off;
+                        if (off < J1) {  // pairs past the range's end are not staged
+                            const uint4* bp = reinterpret_cast<const uint4*>(bin) + 2 * (size_t)src;
+                            const uint4 b0 = bp[0], b1 = bp[1];
+                            s_src[p] = src;
+                            s_r0[p] = b0;
+                            s_r1[p] = b1;
+                            s_view[p] = nv > 1 ? (uint8_t)(src / n_gauss) : (uint8_t)0;
+                            if ((b0.z & b0.w) == 0xffffffffu) {  // RGS_NO_SPANS
+                                rows = (uint32_t)(((int)(int16_t)(b0.y >> 16) >> 4) - ((int)(int16_t)(b0.y & 0xffffu) >> 4) + 1);
+                                large = true;
+                            }
+                        }
+                    } else if (p > nb) {
+                        s_off[p] = 0xffffffffu;  // past the chunk: above every instance index
                     }
-                    const uint32_t before = a > 0 ? s_rcum[b0 + a - 1] : 0u;
-                    tx = (int)s_rc0[b0 + a] + (int)(tt - before);
-                    ty = ty0 + a;
+                    s_rows[p] = (uint16_t)rows;
                 }
-                const int cell = nth_set_bit(s_mask[pl], (int)c);
-                keys[j] = ((s_vto[pl] + (uint32_t)ty * s_vtx[pl] + (uint32_t)tx) << L) |
-                          (uint32_t)vt->v[s_view[pl]].rank_of_cell[cell];
-                vals[j] = ((uint64_t)s_src[pl] << 32) | j;
+                if (t == 0) s_off[nb] = pair_off[r0 + nb];
+                const bool pooled = __syncthreads_or(large) != 0;
+                if (pooled) {  // inclusive scan of the pooled rows over the chunk's pairs
+                    uint32_t inc = wave_incl_scan(s_rows[t]);
+                    if (lane == 63) s_wsum[w] = inc;
+                    __syncthreads();
+                    for (int k = 0; k < w; ++k) inc += s_wsum[k];
+                    s_rend[t] = inc;
+                    __syncthreads();
+                }
+                for (int p0 = 0; p0 < nb && s_off[p0] < J1;) {
+                    int p1 = nb;
+                    uint32_t rbase = 0;
+                    if (pooled) {
+                        // the longest run of pairs from p0 whose pooled rows fit (at least p0 itself)
+                        rbase = p0 > 0 ? s_rend[p0 - 1] : 0u;
+                        int lo = p0 + 1, hi = nb;
+                        while (lo < hi) {
+                            const int mid = (lo + hi + 1) >> 1;
+                            if (s_rend[mid - 1] - rbase <= (uint32_t)ROWPOOL) lo = mid; else hi = mid - 1;
+                        }
+                        p1 = lo;
+                        const uint32_t nrows = s_rend[p1 - 1] - rbase;
+                        // spans of the run's pooled rows, one row per thread
+                        for (uint32_t r = t; r < nrows; r += BN_THREADS) {
+                            const uint32_t g = rbase + r;
+                            int a = p0, b = p1 - 1;  // owner: the first pair whose scan end exceeds g
+                            while (a < b) {
+                                const int mid = (a + b) >> 1;
+                                if (s_rend[mid] > g) b = mid; else a = mid + 1;
+                            }
+                            const float4* rp = reinterpret_cast<const float4*>(rec + (size_t)s_src[a] * RGS_REC_FLOATS);
+                            const float4 ra = rp[0], rb = rp[1];
+                            SpanPre sp;
+                            span_pre(ra.x, ra.y, ra.z, ra.w, rb.x, rb.z, sp);
+                            const uint4 rr = s_r0[a];
+                            const int x_lo = (int)(int16_t)(rr.x & 0xffffu), x_hi = (int)(int16_t)(rr.x >> 16);
+                            const int y_lo = (int)(int16_t)(rr.y & 0xffffu), y_hi = (int)(int16_t)(rr.y >> 16);
+                            const int row = (int)(g - (s_rend[a] - s_rows[a]));
+                            const int2 cs = row_span(sp, x_lo, x_hi, y_lo, y_hi, (y_lo >> 4) + row);
+                            s_rcum[r] = cs.x <= cs.y ? (uint32_t)(cs.y - cs.x + 1) : 0u;
+                            s_rc0[r] = (int16_t)cs.x;
+                        }
+                        __syncthreads();
+                        for (int p = p0 + t; p < p1; p += BN_THREADS) {  // running sums per pooled pair
+                            const uint32_t nr = s_rows[p];
+                            if (nr == 0u) continue;
+                            const uint32_t b0 = s_rend[p] - nr - rbase;
+                            uint32_t run = 0;
+                            for (uint32_t r = 0; r < nr; ++r) {
+                                run += s_rcum[b0 + r];
+                                s_rcum[b0 + r] = run;
+                            }
+                        }
+                        __syncthreads();
+                    }
+                    const uint32_t j0 = s_off[p0] > J0 ? s_off[p0] : J0, j1 = s_off[p1] < J1 ? s_off[p1] : J1;
+                    for (uint32_t j = j0 + t; j < j1; j += BN_THREADS) {
+                        // last pair with s_off[p] <= j (offsets increase; entries past nb are ~0)
+                        int pl = 0;
+#pragma unroll
+                        for (int step = PC / 2; step > 0; step >>= 1)
+                            if (s_off[pl + step] <= j) pl += step;
+                        const uint4 b0 = s_r0[pl], b1 = s_r1[pl];
+                        const uint32_t nt = b1.w;
+                        const uint32_t q = j - s_off[pl];
+                        const uint32_t c = udiv_small(q, nt);
+                        const uint32_t tt = q - c * nt;  // index among the pair's tiles, rows top to bottom
+                        const int tx0 = (int)(int16_t)(b0.x & 0xffffu) >> 4;
+                        const int ty0 = (int)(int16_t)(b0.y & 0xffffu) >> 4;
+                        int tx, ty;
+                        const uint64_t desc = (uint64_t)b0.z | ((uint64_t)b0.w << 32);
+                        if (desc != RGS_NO_SPANS) {
+                            // row of tile tt by byte-wise prefix sums of the 8 row lengths
+                            // (each < 16, total < 128): byte k of `pre` = tiles in rows 0..k,
+                            // and the high bit of byte k of `ge` is set iff pre_k > tt
+                            constexpr uint64_t ONES = 0x0101010101010101ull, HIGH = 0x8080808080808080ull;
+                            const uint64_t lens = (desc >> 4) & 0x0f0f0f0f0f0f0f0full;
+                            const uint64_t pre = lens * ONES;
+                            const uint64_t ge = ((pre | HIGH) - (uint64_t)(tt + 1u) * ONES) & HIGH;
+                            const int k = ge ? (__builtin_ctzll(ge) >> 3) : 7;
+                            const uint32_t before = ((uint32_t)(pre >> (8 * k)) & 0xffu) - ((uint32_t)(lens >> (8 * k)) & 0xffu);
+                            tx = tx0 + (int)((uint32_t)(desc >> (8 * k)) & 15u) + (int)(tt - before);
+                            ty = ty0 + k;
+                        } else {
+                            // pooled rows: the first row whose running sum exceeds tt
+                            const uint32_t rb0 = s_rend[pl] - s_rows[pl] - rbase;
+                            int a = 0, b = (int)s_rows[pl] - 1;
+                            while (a < b) {
+                                const int mid = (a + b) >> 1;
+                                if (s_rcum[rb0 + mid] > tt) b = mid; else a = mid + 1;
+                            }
+                            const uint32_t before = a > 0 ? s_rcum[rb0 + a - 1] : 0u;
+                            tx = (int)s_rc0[rb0 + a] + (int)(tt - before);
+                            ty = ty0 + a;
+                        }
+                        const int cell = nth_set_bit((uint64_t)b1.x | ((uint64_t)b1.y << 32), (int)c);
+                        const int v = s_view[pl];
+                        const uint32_t key = ((s_vto[v] + (uint32_t)ty * s_vtx[v] + (uint32_t)tx) << L) |
+                                             (uint32_t)vt->v[v].rank_of_cell[cell];
+                        keys[j] = key;
+                        srcs[j] = s_src[pl];
+                        atomicAdd(&s_h[key & (NB - 1u)], 1u);
+                    }
+                    if (s_off[p1] >= J1) break;  // uniform: the rest of the chunk lies past the range
+                    __syncthreads();             // the pool is reused by the next run
+                    p0 = p1;
+                }
+                const bool last = s_off[nb] >= J1;
+                __syncthreads();  // the chunk's arrays are reused by the next one
+                if (last) break;
             }
-            __syncthreads();  // the pool is reused by the next run
-            p0 = p1;
+            if (t < NB) {
+                if (FOLD) {
+                    if (s_h[t]) atomicAdd(&tab.hist[(int64_t)(j00 / (BN_THREADS * items)) * NB + t], s_h[t]);
+                } else {
+                    radix_tile_counts(tab, NB, range, t, s_h[t], dsum);
+                }
+            }
+            __syncthreads();  // the counts are cleared for the next range
         }
+        if (!FOLD && t < NB) radix_unit_counts(tab, NB, 0, unit, t, dsum);
     }
 }
 
@@ -586,6 +640,8 @@ size_t bin_ws_bytes(int64_t n, int n_views, int64_t total_tiles, int L, int64_t 
     c.take<uint32_t>(dense + 1);      // dense start
     c.take<uint32_t>(dense + 1);      // dense end
     c.take<uint32_t>(NCLS_WORDS);     // slot and tile size classes
+    c.take<uint32_t>(capacity / RGS_RADIX_TILE + 1);  // the pair at the start of each tile of instances
+    c.take<uint32_t>(RGS_FOLD_KEYS / RGS_FIRST_GROUP);  // and of each small group
     const int64_t big = m > capacity ? m : capacity;
     const int64_t big2 = big > dense ? big : dense;
     c.take<char>(radix_ws_bytes(big2 + 1));
@@ -615,6 +671,8 @@ rgs_status bin_sort(const rgs_projected* proj, int64_t n, int n_views, const Vie
     uint32_t* dstart = c.take<uint32_t>(dense + 1);
     uint32_t* dend = c.take<uint32_t>(dense + 1);
     uint32_t* cls = c.take<uint32_t>(NCLS_WORDS);
+    uint32_t* first = c.take<uint32_t>(bins->capacity / RGS_RADIX_TILE + 1);
+    uint32_t* first_small = c.take<uint32_t>(RGS_FOLD_KEYS / RGS_FIRST_GROUP);
     const int64_t big = m > bins->capacity ? m : bins->capacity;
     const int64_t big2 = big > dense ? big : dense;
     void* rws = c.take<char>(radix_ws_bytes(big2 + 1));
@@ -637,27 +695,32 @@ rgs_status bin_sort(const rgs_projected* proj, int64_t n, int n_views, const Vie
         hipLaunchKernelGGL(k_vis_count, dim3((unsigned)vtiles), dim3(BN_THREADS), 0, s, proj->count, m, pos);
     if (m <= 0 || !vfold)
         if ((st = scan_tile_sums(pos, DevN{nullptr, m, 1, 1}, VC_TILE, &cnt[0], s)) != RGS_OK) return st;
+    // several views: one more pass, by view, which makes their number odd, so the
+    // compaction writes to the alt buffers; the result is in zkey / pair_src
+    const bool views = n_views > 1;
+    uint32_t *zk = views ? zkey_alt : zkey, *zk2 = views ? zkey : zkey_alt;
+    uint32_t *sr = views ? src_alt : bins->pair_src, *sr2 = views ? bins->pair_src : src_alt;
     if (m > 0)
         hipLaunchKernelGGL(k_vis_compact, dim3((unsigned)vtiles), dim3(BN_THREADS), 0, s, proj->count, proj->depth, m, pos,
-                           vfold ? 1 : 0, &cnt[0], zkey, bins->pair_src);
+                           vfold ? 1 : 0, &cnt[0], zk, sr);
     RGS_LAUNCH_CHECK();
-    if ((st = radix_sort_u32_u32_dev(zkey, bins->pair_src, zkey_alt, src_alt, &cnt[0], m, 32, rws, s)) != RGS_OK)
-        return st;
-    if (n_views > 1) {
-        hipLaunchKernelGGL(k_view_keys, dgrid(m), dim3(BN_THREADS), 0, s, bins->pair_src, &cnt[0], n, zkey);
-        if ((st = radix_sort_u32_u32_dev(zkey, bins->pair_src, zkey_alt, src_alt, &cnt[0], m, bits_for(n_views), rws, s)) !=
-            RGS_OK)
+    if ((st = radix_sort_u32_u32(zk, sr, zk2, sr2, m, &cnt[0], radix_plan(m, 32), rws, s)) != RGS_OK) return st;
+    if (views) {
+        hipLaunchKernelGGL(k_view_keys, dgrid(m), dim3(BN_THREADS), 0, s, sr, &cnt[0], n, zk);
+        if ((st = radix_sort_u32_u32(zkey, bins->pair_src, zkey_alt, src_alt, m, &cnt[0], radix_plan(m, bits_for(n_views)),
+                                     rws, s)) != RGS_OK)
             return st;
     }
     // 2. instance offsets per ordered pair; the instance count goes to the host
     // (with the empty marks of the dense slot table: dstart = ~0)
     if (m > 0)
         hipLaunchKernelGGL(k_pair_counts, dgrid(m), dim3(BN_THREADS), 0, s, bins->pair_src, &cnt[0], proj->count,
-                           bins->pair_rank, flag, reinterpret_cast<uint32_t*>(sws), dstart, dense);
+                           bins->pair_rank, flag, reinterpret_cast<uint32_t*>(sws), dstart, dense,
+                           reinterpret_cast<uint32_t*>(rws), radix_fold_words(bins->capacity));
     else
         hipLaunchKernelGGL(k_fill_u32, grid(dense), dim3(BN_THREADS), 0, s, dstart, dense, 0xffffffffu);
     // with the tail of pair_off and, without a host copy, the capacity guard
-    const ScanTail tail{cnt, sync ? 0 : 1, bins->capacity};
+    const ScanTail tail{cnt, sync ? 0 : 1, bins->capacity, first, first_small};
     // (k_pair_counts wrote the tile sums; without pairs the scan reads none)
     if ((st = exclusive_scan_u32_dev(flag, bins->pair_off, DevN{&cnt[0], m, 1, 1}, m, &cnt[1], sws, s, 0, &tail, 1)) !=
         RGS_OK)
@@ -679,16 +742,35 @@ rgs_status bin_sort(const rgs_projected* proj, int64_t n, int n_views, const Vie
         slot_bound = n_inst < dense ? n_inst : dense;
     }
 
-    // 3. emit and sort instances by (tile, rank)
-    if (m > 0)
-        hipLaunchKernelGGL(k_emit, dgrid(m), dim3(BN_THREADS), 0, s, bins->pair_src, &cnt[0], bins->pair_off, proj->rec,
-                           proj->bin, n, vt_dev, bins->keys, bins->vals);
-    RGS_LAUNCH_CHECK();
+    // 3. emit and sort instances by (tile, rank); the emission writes where the
+    // sort's passes start, so that they end in keys / vals
     const int key_bits = L + bits_for((uint64_t)total_tiles);
     if (key_bits > 32) return RGS_E_UNSUPPORTED;
-    if (sync) st = radix_sort_u32_u64(bins->keys, bins->vals, keys_alt, vals_alt, n_inst, key_bits, rws, s);
-    else st = radix_sort_u32_u64_dev(bins->keys, bins->vals, keys_alt, vals_alt, &cnt[1], n_inst, key_bits, rws, s);
-    if (st != RGS_OK) return st;
+    const RadixPlan plan = radix_plan(n_inst, key_bits > 0 ? key_bits : 1);
+    if (m > 0 && n_inst > 0) {
+        const bool odd = plan.passes & 1;
+        uint32_t* ek = odd ? keys_alt : bins->keys;
+        uint32_t* ev = reinterpret_cast<uint32_t*>(odd ? vals_alt : bins->vals);
+        const int64_t ranges = plan.fold ? (n_inst + RGS_FIRST_GROUP - 1) / RGS_FIRST_GROUP : plan.tiles;
+        const dim3 eg((unsigned)(ranges < 16384 ? ranges : 16384));
+        const RadixWs rw = radix_ws(rws, plan);
+#define RGS_EMIT(B, F)                                                                                                    \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_emit<B, F>), eg, dim3(BN_THREADS), 0, s, bins->pair_src, cnt, bins->pair_off, plan.fold ? first_small : first, \
+                       proj->rec, proj->bin, (uint32_t)n, vt_dev, plan.items, rw.a, rw.b, ek, ev)
+        switch (plan.bits[0] + (plan.fold ? 16 : 0)) {
+            case 6: RGS_EMIT(6, false); break;
+            case 7: RGS_EMIT(7, false); break;
+            case 8: RGS_EMIT(8, false); break;
+            case 16 + 6: RGS_EMIT(6, true); break;
+            case 16 + 7: RGS_EMIT(7, true); break;
+            default: RGS_EMIT(8, true); break;
+        }
+#undef RGS_EMIT
+        RGS_LAUNCH_CHECK();
+        if ((st = radix_sort_instances(bins->keys, bins->vals, keys_alt, vals_alt, n_inst, sync ? nullptr : &cnt[1], plan, rws,
+                                       s)) != RGS_OK)
+            return st;
+    }
 
     // 4. slots (k_slot_bounds also clears the size-class counters): the tile
     // sums of the slot marks, then the slot table and the class counts

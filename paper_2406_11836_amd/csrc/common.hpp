@@ -212,11 +212,21 @@ size_t scan_ws_bytes(int64_t n);
 // Optional tail of the scan of per-pair instance counts (counters cnt =
 // [pairs, instances, slots, required]; the scan's total must be &cnt[1]):
 // out[pairs] = total and the capacity guard (see k_scan_apply).
+// first, if not null: first[t] = the pair that holds instance RGS_RADIX_TILE t,
+// for every such instance below the capacity; first_small[t] = the pair that
+// holds instance RGS_FIRST_GROUP t below RGS_FOLD_KEYS.
 struct ScanTail {
     uint32_t* cnt;
     int guard;
     int64_t capacity;
+    uint32_t *first, *first_small;
 };
+// Keys per tile of the radix sort (512 for small sorts), the largest sort whose
+// scatter adds up the tiles' counts itself, and the instances per block of the
+// emission for such a sort.
+static constexpr int RGS_RADIX_TILE = 2048;
+static constexpr int64_t RGS_FOLD_KEYS = 128 * RGS_RADIX_TILE;
+static constexpr int RGS_FIRST_GROUP = 256;
 // Elements per tile of the scans below.
 static constexpr int64_t RGS_SCAN_TILE = 4096;
 // out[i] = sum_{j<i} in[j]; if total != nullptr, *total (device) = sum of all.
@@ -234,15 +244,67 @@ rgs_status scan_tile_sums(uint32_t* partial, DevN dn, int64_t tile, uint32_t* to
 // ... and the sums of the RGS_SCAN_TILE-element tiles of in[0, n) (marks as above).
 rgs_status scan_tile_reduce(const uint32_t* in, int64_t n, int marks, uint32_t* partial, hipStream_t s);
 size_t radix_ws_bytes(int64_t n);
-// Stable LSD sort of (key, value) by key bits [0, bits); the result ends in
-// keys/vals (the alt buffers are scratch of the same size).
-rgs_status radix_sort_u32_u64(uint32_t* keys, uint64_t* vals, uint32_t* keys_alt, uint64_t* vals_alt,
-                              int64_t n, int bits, void* ws, hipStream_t s);
-rgs_status radix_sort_u32_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                              int64_t n, int bits, void* ws, hipStream_t s);
-// The same, with n read on the device (upper bound n_max for the grid).
-rgs_status radix_sort_u32_u64_dev(uint32_t* keys, uint64_t* vals, uint32_t* keys_alt, uint64_t* vals_alt,
-                                  const uint32_t* n_dev, int64_t n_max, int bits, void* ws, hipStream_t s);
-rgs_status radix_sort_u32_u32_dev(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                                  const uint32_t* n_dev, int64_t n_max, int bits, void* ws, hipStream_t s);
+// Passes and digit widths of a sort of at most n keys by `bits` key bits; items
+// = keys per thread (a tile is 256 items), tiles = tiles of n keys.
+struct RadixPlan {
+    int passes, bits[4], items, fold;
+    int64_t tiles;
+};
+RadixPlan radix_plan(int64_t n, int bits);
+// Words of the table of a sort of at most `capacity` keys that may be folded.
+int radix_fold_words(int64_t capacity);
+
+// A pass's table of digit counts.  fold: one row per tile, which the scatter
+// adds up itself.  Else one row per digit over units of `per` tiles; from
+// RADIX_WIDE keys on a unit is 16 tiles, and the counts of the tiles before a
+// tile in its unit have a row per tile (tpre): the [digit][tile] table of one
+// row per digit costs a 4-byte write and read at a stride per (digit, tile)
+// (about 0.7G instances, three passes: row scans 1.6 -> 0.1 ms; from 16M keys on
+// or below there is no difference, and fewer units than blocks on the chip).
+static constexpr int64_t RADIX_WIDE = 32000000;
+struct RadixTab {
+    uint32_t *hist, *offs, *tpre;
+    int units, per, shift;  // per = 1 << shift
+};
+__device__ __forceinline__ RadixTab radix_tab(int64_t n, int items, int fold, uint32_t* ws_a, uint32_t* ws_b) {
+    RadixTab t;
+    const int64_t tiles = (n + 256 * items - 1) / (256 * items);
+    const bool wide = n >= RADIX_WIDE && !fold;
+    t.shift = wide ? 4 : 0;
+    t.per = 1 << t.shift;
+    t.units = (int)((tiles + t.per - 1) >> t.shift);
+    t.hist = wide ? ws_b : ws_a;
+    t.offs = wide ? ws_b + 256 * (int64_t)t.units : ws_b;
+    t.tpre = ws_a;
+    return t;
+}
+// A producer's count of one digit in one tile; run: the unit's count so far.
+__device__ __forceinline__ void radix_tile_counts(const RadixTab& t, int digits, int tile, int digit, uint32_t c,
+                                                  uint32_t& run) {
+    if (t.per > 1) t.tpre[(int64_t)tile * digits + digit] = run;
+    run += c;
+}
+__device__ __forceinline__ void radix_unit_counts(const RadixTab& t, int digits, int fold, int unit, int digit, uint32_t run) {
+    t.hist[fold ? (int64_t)unit * digits + digit : (int64_t)digit * t.units + unit] = run;
+}
+// Elements with this digit before the tile (not fold).
+__device__ __forceinline__ uint32_t radix_tile_offset(const RadixTab& t, int digits, int tile, int digit) {
+    const uint32_t o = t.offs[(int64_t)digit * t.units + (tile >> t.shift)];
+    return t.per > 1 ? o + t.tpre[(int64_t)tile * digits + digit] : o;
+}
+
+struct RadixWs {
+    uint32_t *a, *b, *dtot;
+};
+RadixWs radix_ws(void* ws, const RadixPlan& p);
+// Stable LSD sort of (key, value) by the plan's key bits; n elements, or *n_dev
+// of at most n.  The input is in keys / vals if the passes are even, else in the
+// alt buffers; the result is in keys / vals.
+rgs_status radix_sort_u32_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t n,
+                              const uint32_t* n_dev, const RadixPlan& p, void* ws, hipStream_t s);
+// The instances: the input values are 4-byte sources at the start of the value
+// buffer, element i becomes (source << 32) | i, and ws holds the first pass's
+// histogram.
+rgs_status radix_sort_instances(uint32_t* keys, uint64_t* vals, uint32_t* keys_alt, uint64_t* vals_alt, int64_t n,
+                                const uint32_t* n_dev, const RadixPlan& p, void* ws, hipStream_t s);
 }  // namespace rgs

@@ -143,7 +143,8 @@ rgs_status group_by_cell(const rgs_gaussians* in, const rgs_kdtree* kd, int L, c
     hipLaunchKernelGGL(k_group_keys, dim3(grid), dim3(LY_THREADS), 0, s, in->means, kd->center_cell, kd->cell_bounds,
                        1 << L, n, keys, idx);
     RGS_LAUNCH_CHECK();
-    rgs_status st = radix_sort_u32_u32(keys, idx, keys_alt, idx_alt, n, 24 + L, rws, s);
+    // 24 + L bits: four passes, an even number, so the input starts in keys / idx
+    rgs_status st = radix_sort_u32_u32(keys, idx, keys_alt, idx_alt, n, nullptr, radix_plan(n, 25 > 24 + L ? 25 : 24 + L), rws, s);
     if (st != RGS_OK) return st;
     const int rows = 11 + 3 * (in->sh_degree + 1) * (in->sh_degree + 1);
     for (int r = 0; r < rows; r += LY_ROWS) {

@@ -4,14 +4,15 @@
 // scan each tile with its offset.  Tiles are staged through LDS so that
 // global loads and stores stay coalesced.
 //
-// Radix sort: 8-bit digits, least significant first.  Per pass a histogram
-// kernel counts digits per 2048-key tile (LDS atomics on integers), one
-// block per digit scans that digit's row of the [256][tiles] table (the
-// digit bases come from the 256 row totals), and a scatter kernel ranks each
-// key stably inside its tile: every wave walks its strip in order, finds the
-// lanes sharing its digit with eight ballots, and keeps a running count per
+// Radix sort: digits of up to 8 bits, least significant first.  Per pass a
+// histogram kernel counts digits per tile (LDS atomics on integers), one
+// block per digit scans that digit's row of the [digit][tile] table (the digit
+// bases come from the row totals), and a scatter kernel ranks each key stably
+// inside its tile: every wave walks its strip in order, finds the lanes
+// sharing its digit with a ballot per digit bit, and keeps a running count per
 // digit in LDS; keys are then reordered in LDS by digit so that the global
-// writes come out as contiguous runs.
+// writes come out as contiguous runs.  A sort of few tiles skips the row scan;
+// the instance sort's first histogram comes from the emission.
 #include "common.hpp"
 
 namespace rgs {
@@ -174,6 +175,23 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_apply(const uint32_t* __r
             int64_t i = base + li;
             if (i < n) out[i] = s[skew(li)];
         }
+        if (tail.first) {
+            // the pair holding each group's first instance: the last whose offset is
+            // not above it (entries past n hold the tile's end)
+            const int64_t end0 = (int64_t)toff + tsum, end = end0 < tail.capacity ? end0 : tail.capacity;
+            auto mark = [&](uint32_t* table, int64_t group, int64_t lim) {
+                for (int64_t g = ((int64_t)toff + group - 1) / group + threadIdx.x; g * group < lim; g += SCAN_THREADS) {
+                    const uint32_t j = (uint32_t)(g * group);
+                    int p = 0;
+#pragma unroll
+                    for (int step = SCAN_TILE / 2; step > 0; step >>= 1)
+                        if (s[skew(p + step)] <= j) p += step;
+                    table[g] = (uint32_t)(base + p);
+                }
+            };
+            mark(tail.first, RGS_RADIX_TILE, end);
+            mark(tail.first_small, RGS_FIRST_GROUP, end < RGS_FOLD_KEYS ? end : RGS_FOLD_KEYS);
+        }
         __syncthreads();  // LDS is reused by the next tile
     }
 }
@@ -209,7 +227,7 @@ static constexpr int64_t SCAN_FOLD_TILES = 1024;
 rgs_status exclusive_scan_u32_dev(const uint32_t* in, uint32_t* out, DevN dn, int64_t n_max, uint32_t* total, void* ws,
                                   hipStream_t s, int marks, const ScanTail* tail, int sums_ready) {
     uint32_t* partial = reinterpret_cast<uint32_t*>(ws);
-    const ScanTail tl = tail ? *tail : ScanTail{nullptr, 0, 0};
+    const ScanTail tl = tail ? *tail : ScanTail{nullptr, 0, 0, nullptr, nullptr};
     const int64_t tiles = (n_max + SCAN_TILE - 1) / SCAN_TILE;
     const bool fold = tiles <= SCAN_FOLD_TILES;
     const unsigned grid = (unsigned)(tiles < 1 ? 1 : (dn.p && tiles > DEV_GRID ? DEV_GRID : tiles));
@@ -232,9 +250,39 @@ rgs_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint
 
 // ------------------------------------------------------------------ radix sort
 static constexpr int RS_THREADS = 256;
-static constexpr int RS_ITEMS = 8;
-static constexpr int RS_TILE = RS_THREADS * RS_ITEMS;  // 2048 keys per block
-static constexpr int RS_WAVE_ITEMS = 64 * RS_ITEMS;    // a wave's strip
+
+// The passes of a sort: as few as 8-bit digits allow, of nearly equal widths
+// (13 bits: 7 + 6, not 8 + 5), so that the runs a tile writes per digit are as
+// long as they can be.  Tiles are 2048 keys; a sort of at most 64K keys takes
+// 512-key tiles, since a few blocks' latency is all it costs (20k keys, four
+// passes' scatters: 24 against 31 us).
+// Up to RS_FOLD_TILES tiles the scatter adds up the earlier tiles' counts
+// itself (no column scan launch, about 4 us).
+static constexpr int64_t RS_SMALL_KEYS = 65536;
+static constexpr int64_t RS_FOLD_TILES = RGS_FOLD_KEYS / RGS_RADIX_TILE;
+
+RadixPlan radix_plan(int64_t n, int bits) {
+    RadixPlan p;
+    p.passes = (bits + 7) / 8;
+    int left = bits;
+    for (int k = 0; k < 4; ++k) {
+        const int w = k < p.passes ? (left + (p.passes - k) - 1) / (p.passes - k) : 0;
+        p.bits[k] = w > 0 && w < 6 ? 6 : w;
+        left -= p.bits[k];
+        if (left < 0) left = 0;
+    }
+    p.items = n <= RS_SMALL_KEYS ? 2 : RGS_RADIX_TILE / RS_THREADS;
+    p.tiles = (n + RS_THREADS * p.items - 1) / (RS_THREADS * p.items);
+    p.fold = p.tiles <= RS_FOLD_TILES ? 1 : 0;
+    return p;
+}
+
+int radix_fold_words(int64_t capacity) {
+    const int64_t small = capacity < RS_SMALL_KEYS ? capacity : RS_SMALL_KEYS;
+    const int64_t a = (capacity + RGS_RADIX_TILE - 1) / RGS_RADIX_TILE, b = (small + 2 * RS_THREADS - 1) / (2 * RS_THREADS);
+    const int64_t t = a > b ? a : b;
+    return (int)(256 * (t < RS_FOLD_TILES ? t : RS_FOLD_TILES));
+}
 
 __device__ __forceinline__ int64_t rs_n(int64_t n, const uint32_t* n_dev) {
     return n_dev ? (int64_t)*n_dev : n;
@@ -247,51 +295,78 @@ __device__ __forceinline__ int64_t rs_n(int64_t n, const uint32_t* n_dev) {
 // round) every XCD takes one contiguous band of tiles, the same number each,
 // so that the tiles that write neighbouring parts of a digit's output run on
 // one XCD and the cache lines their runs share are completed in one L2.
+template <int BITS, int ITEMS>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint32_t* __restrict__ keys, int64_t n_host,
-                                                        const uint32_t* __restrict__ n_dev, int shift,
-                                                        uint32_t* __restrict__ hist, int ntiles) {
-    __shared__ uint32_t s_h[256];
+                                                        const uint32_t* __restrict__ n_dev, int shift, int fold,
+                                                        uint32_t* __restrict__ ws_a, uint32_t* __restrict__ ws_b) {
+    constexpr int NB = 1 << BITS, TILE = RS_THREADS * ITEMS;
+    __shared__ uint32_t s_h[NB];
     const int64_t n = rs_n(n_host, n_dev);
-    // with a device count the table is [256][tiles in use]
-    if (n_dev) ntiles = (int)((n + RS_TILE - 1) / RS_TILE);
-    for (int nth = blockIdx.x; nth < ntiles; nth += gridDim.x) {
-        const int tile = xcd_band(nth, ntiles);
-        s_h[threadIdx.x] = 0;
-        __syncthreads();
-        const int64_t base = (int64_t)tile * RS_TILE;
-        // all loads first (a lane past the end reads the last key and adds nothing)
-        uint32_t kv[RS_ITEMS];
+    const RadixTab tab = radix_tab(n, ITEMS, fold, ws_a, ws_b);
+    for (int nth = blockIdx.x; nth < tab.units; nth += gridDim.x) {
+        const int unit = xcd_band(nth, tab.units);
+        uint32_t run = 0;  // digit threadIdx.x's count over the unit's tiles so far
+        for (int u = 0; u < tab.per; ++u) {
+            const int tile = unit * tab.per + u;
+            const int64_t base = (int64_t)tile * TILE;
+            if (base >= n) break;  // uniform per block
+            if (threadIdx.x < NB) s_h[threadIdx.x] = 0;
+            __syncthreads();
+            // all loads first (a lane past the end reads the last key and adds nothing)
+            const uint32_t tile_n = (uint32_t)((n - base) < TILE ? (n - base) : TILE);
+            const uint32_t* kp = keys + base;
+            uint32_t kv[ITEMS];
 #pragma unroll
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            const int64_t i = base + k * RS_THREADS + threadIdx.x;
-            kv[k] = keys[i < n ? i : n - 1];
+            for (int k = 0; k < ITEMS; ++k) {
+                const uint32_t i = k * RS_THREADS + threadIdx.x;
+                kv[k] = kp[i < tile_n ? i : tile_n - 1u];
+            }
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) {
+                const uint32_t d = (kv[k] >> shift) & (NB - 1u);
+                bool add = k * RS_THREADS + threadIdx.x < tile_n;
+                if (tab.per > 1) {
+                    // a large sort's later digits (view, screen rows) hardly vary inside
+                    // a wave, and LDS atomics on one address take a lane per clock: the
+                    // two commonest-looking digits are counted by ballot
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const uint64_t am = __builtin_amdgcn_ballot_w64(add);
+                        if (am == 0ull) break;
+                        const int l = (int)__builtin_ctzll(am);
+                        const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)d, l);
+                        const uint64_t m = __builtin_amdgcn_ballot_w64(add && d == f);
+                        if ((int)(threadIdx.x & 63) == l) atomicAdd(&s_h[f], (uint32_t)__popcll(m));
+                        add = add && d != f;
+                    }
+                }
+                if (add) atomicAdd(&s_h[d], 1u);
+            }
+            __syncthreads();
+            if (threadIdx.x < NB) radix_tile_counts(tab, NB, tile, threadIdx.x, s_h[threadIdx.x], run);
         }
-#pragma unroll
-        for (int k = 0; k < RS_ITEMS; ++k)
-            if (base + k * RS_THREADS + threadIdx.x < n) atomicAdd(&s_h[(kv[k] >> shift) & 0xffu], 1u);
-        __syncthreads();
-        hist[(int64_t)threadIdx.x * ntiles + tile] = s_h[threadIdx.x];
+        if (threadIdx.x < NB) radix_unit_counts(tab, NB, fold, unit, threadIdx.x, run);
         __syncthreads();
     }
 }
 
-// Per digit d (one block each): exclusive scan over tiles of the digit's row
+// Per digit d (one block each): exclusive scan over units of the digit's row
 // hist[d][*] into offs[d][*], and the row total into dtot[d].  The scatter
-// adds the digit's base (an exclusive scan of the 256 totals, done in LDS).
-__global__ __launch_bounds__(RS_THREADS) void k_rs_colscan(const uint32_t* __restrict__ hist, int64_t n_host,
-                                                           const uint32_t* __restrict__ n_dev, int ntiles,
-                                                           uint32_t* __restrict__ offs, uint32_t* __restrict__ dtot) {
+// adds the digit's base (an exclusive scan of the totals, done in LDS).
+__global__ __launch_bounds__(RS_THREADS) void k_rs_colscan(int64_t n_host, const uint32_t* __restrict__ n_dev, int items,
+                                                           uint32_t* __restrict__ ws_a, uint32_t* __restrict__ ws_b,
+                                                           uint32_t* __restrict__ dtot) {
     __shared__ uint32_t s_wave[4];
-    const int64_t n = rs_n(n_host, n_dev);
-    if (n_dev) ntiles = (int)((n + RS_TILE - 1) / RS_TILE);
-    const int64_t row = (int64_t)blockIdx.x * ntiles;
+    const RadixTab tab = radix_tab(rs_n(n_host, n_dev), items, 0, ws_a, ws_b);
+    const int units = tab.units;
+    const int64_t row = (int64_t)blockIdx.x * units;
     uint32_t carry = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += RS_THREADS * 4) {
+    for (int t0 = 0; t0 < units; t0 += RS_THREADS * 4) {
         uint32_t v[4], acc = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int t = t0 + threadIdx.x * 4 + k;
-            v[k] = t < ntiles ? hist[row + t] : 0u;
+            v[k] = t < units ? tab.hist[row + t] : 0u;
             acc += v[k];
         }
         uint32_t ex;
@@ -300,7 +375,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_colscan(const uint32_t* __res
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int t = t0 + threadIdx.x * 4 + k;
-            if (t < ntiles) offs[row + t] = run;
+            if (t < units) tab.offs[row + t] = run;
             run += v[k];
         }
         carry += tot;
@@ -308,96 +383,142 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_colscan(const uint32_t* __res
     if (threadIdx.x == 0) dtot[blockIdx.x] = carry;
 }
 
-template <typename V>
+// The value an element enters the sort with: as stored, or, for the instance
+// sort's first pass, (source << 32) | position from the 4-byte source alone
+// (4 + 4 bytes per instance are emitted and read instead of 4 + 8).
+template <typename VIN, typename V>
+__device__ __forceinline__ V rs_value(VIN v, int64_t i) {
+    if constexpr (sizeof(VIN) == sizeof(V)) return (V)v;
+    else return ((V)v << 32) | (V)(uint32_t)i;
+}
+
+// (A bound of five or six waves per SIMD, which the LDS would allow, spills: 47
+// against 42 us per pass of 7.3M instances.)
+template <typename VIN, typename V, int BITS, int ITEMS, bool FOLD>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const uint32_t* __restrict__ keys_in,
-                                                           const V* __restrict__ vals_in, int64_t n_host,
+                                                           const VIN* __restrict__ vals_in, int64_t n_host,
                                                            const uint32_t* __restrict__ n_dev, int shift,
-                                                           const uint32_t* __restrict__ offsets,
-                                                           const uint32_t* __restrict__ dtot, int ntiles,
+                                                           uint32_t* __restrict__ ws_a, uint32_t* __restrict__ ws_b,
+                                                           const uint32_t* __restrict__ dtot,
                                                            uint32_t* __restrict__ keys_out,
                                                            V* __restrict__ vals_out) {
-    __shared__ uint32_t s_cnt[4][256];  // per-wave running digit counts, then wave prefixes
-    __shared__ uint32_t s_dstart[256];  // tile-local start of each digit
-    __shared__ uint32_t s_goff[256];    // global start of each digit for this tile
-    __shared__ uint32_t s_dbase[256];   // global start of each digit
+    constexpr int NB = 1 << BITS, TILE = RS_THREADS * ITEMS;
+    __shared__ uint32_t s_cnt[4][NB];   // per-wave running digit counts, then wave prefixes
+    __shared__ uint32_t s_dstart[NB];   // tile-local start of each digit
+    __shared__ uint32_t s_goff[NB];     // global start of each digit for this tile
+    __shared__ uint32_t s_dbase[NB];    // global start of each digit
     __shared__ uint32_t s_wave[4];
-    __shared__ uint32_t s_keys[RS_TILE];
-    __shared__ V s_vals[RS_TILE];
+    __shared__ uint32_t s_keys[TILE];
+    __shared__ V s_vals[TILE];
 
     const int64_t n = rs_n(n_host, n_dev);
-    if (n_dev) ntiles = (int)((n + RS_TILE - 1) / RS_TILE);
+    const RadixTab tab = radix_tab(n, ITEMS, FOLD ? 1 : 0, ws_a, ws_b);
+    const int tiles = (int)((n + TILE - 1) / TILE);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if ((int)blockIdx.x < ntiles) {  // the block has a tile (uniform per block)
+    if (!FOLD && (int)blockIdx.x < tiles) {  // the block has a tile (uniform per block)
         uint32_t ex;
-        block_excl_scan_256(dtot[threadIdx.x], s_wave, &ex);
-        s_dbase[threadIdx.x] = ex;
+        block_excl_scan_256(threadIdx.x < NB ? dtot[threadIdx.x] : 0u, s_wave, &ex);
+        if (threadIdx.x < NB) s_dbase[threadIdx.x] = ex;
     }
-    for (int nth = blockIdx.x; nth < ntiles; nth += gridDim.x) {
-        const int tile = xcd_band(nth, ntiles);
-        for (int k = threadIdx.x; k < 4 * 256; k += RS_THREADS) (&s_cnt[0][0])[k] = 0;
+    for (int nth = blockIdx.x; nth < tiles; nth += gridDim.x) {
+        const int tile = xcd_band(nth, tiles);
+        for (int k = threadIdx.x; k < 4 * NB; k += RS_THREADS) (&s_cnt[0][0])[k] = 0;
         __syncthreads();
 
-        const int64_t base = (int64_t)tile * RS_TILE;
-        const int64_t tile_n = (n - base) < RS_TILE ? (n - base) : RS_TILE;
-        uint32_t key[RS_ITEMS];
-        V val[RS_ITEMS];
-        uint32_t rank[RS_ITEMS];
+        const int64_t base = (int64_t)tile * TILE;
+        const uint32_t tile_n = (uint32_t)((n - base) < TILE ? (n - base) : TILE);
+        const uint32_t* kp = keys_in + base;
+        const VIN* vp = vals_in + base;
+        const uint32_t l0 = (uint32_t)w * (64 * ITEMS) + (uint32_t)lane;  // the thread's first element of the tile
+        uint32_t key[ITEMS];
+        V val[ITEMS];
+        uint32_t rank[ITEMS];
         // all loads first, without branches (a lane past the end reads the last element)
 #pragma unroll
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            const int64_t i = base + (int64_t)w * RS_WAVE_ITEMS + k * 64 + lane;
-            const int64_t ic = i < n ? i : n - 1;
-            key[k] = keys_in[ic];
-            val[k] = vals_in[ic];
+        for (int k = 0; k < ITEMS; ++k) {
+            const uint32_t li = l0 + k * 64, lc = li < tile_n ? li : tile_n - 1u;
+            key[k] = kp[lc];
+            val[k] = rs_value<VIN, V>(vp[lc], base + lc);
         }
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            const int64_t i = base + (int64_t)w * RS_WAVE_ITEMS + k * 64 + lane;
-            const bool valid = i < n;
-            const uint32_t d = (key[k] >> shift) & 0xffu;
-            uint64_t m = __ballot(valid);
-    #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t bb = __ballot(bit);
-                m &= bit ? bb : ~bb;
+        uint32_t tot = 0, prior_tiles = 0;
+        if (FOLD && threadIdx.x < NB) {
+            // the tiles' counts, tile-major: the earlier tiles' sum and the total
+            constexpr int FU = 32;  // loads in flight
+            for (int t0 = 0; t0 < tiles; t0 += FU) {
+                uint32_t x[FU];
+#pragma unroll
+                for (int k = 0; k < FU; ++k) x[k] = tab.hist[(t0 + k < tiles ? t0 + k : 0) * NB + threadIdx.x];
+#pragma unroll
+                for (int k = 0; k < FU; ++k) {
+                    tot += t0 + k < tiles ? x[k] : 0u;
+                    prior_tiles += t0 + k < tile ? x[k] : 0u;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const bool valid = l0 + k * 64 < tile_n;
+            const uint32_t d = (key[k] >> shift) & (NB - 1u);
+            // the lanes with the same digit: per digit bit, its ballot where the lane's
+            // bit is set, else the ballot's complement (sx = -1 or 0)
+            const uint64_t vb = __builtin_amdgcn_ballot_w64(valid);
+            uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
+#pragma unroll
+            for (int b = 0; b < BITS; ++b) {
+                const uint32_t sx = (uint32_t)__builtin_amdgcn_sbfe((int)key[k], (uint32_t)(shift + b), 1u);
+                const uint64_t bb = __builtin_amdgcn_ballot_w64(sx != 0u);
+                lo &= ~((uint32_t)bb ^ sx);
+                hi &= ~((uint32_t)(bb >> 32) ^ sx);
             }
             uint32_t prior = 0;
             if (valid) prior = s_cnt[w][d];
-            rank[k] = prior + (uint32_t)__popcll(m & lt_mask);
+            const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            const uint32_t all = (uint32_t)(__popc(lo) + __popc(hi));
+            rank[k] = prior + before;
             // the highest lane of each digit group publishes the new count
-            if (valid && (m >> lane) == 1ull) s_cnt[w][d] = prior + (uint32_t)__popcll(m);
-            if (!valid) rank[k] = 0xffffffffu;
+            if (valid && before + 1u == all) s_cnt[w][d] = prior + all;
+        }
+        if (FOLD) {
+            uint32_t ex;
+            block_excl_scan_256(tot, s_wave, &ex);
+            if (threadIdx.x < NB) s_goff[threadIdx.x] = ex + prior_tiles;
         }
         __syncthreads();
         {
             const int d = threadIdx.x;
-            const uint32_t c0 = s_cnt[0][d], c1 = s_cnt[1][d], c2 = s_cnt[2][d], c3 = s_cnt[3][d];
-            s_cnt[0][d] = 0;
-            s_cnt[1][d] = c0;
-            s_cnt[2][d] = c0 + c1;
-            s_cnt[3][d] = c0 + c1 + c2;
-            const uint32_t tot = c0 + c1 + c2 + c3;
-            s_goff[d] = s_dbase[d] + offsets[(int64_t)d * ntiles + tile];
+            uint32_t c = 0;
+            if (d < NB) {
+                const uint32_t c0 = s_cnt[0][d], c1 = s_cnt[1][d], c2 = s_cnt[2][d], c3 = s_cnt[3][d];
+                s_cnt[0][d] = 0;
+                s_cnt[1][d] = c0;
+                s_cnt[2][d] = c0 + c1;
+                s_cnt[3][d] = c0 + c1 + c2;
+                c = c0 + c1 + c2 + c3;
+                if (!FOLD) s_goff[d] = s_dbase[d] + radix_tile_offset(tab, NB, tile, d);
+            }
             uint32_t ex;
-            block_excl_scan_256(tot, s_wave, &ex);
-            s_dstart[d] = ex;
+            block_excl_scan_256(c, s_wave, &ex);
+            if (d < NB) {
+                s_dstart[d] = ex;
+                s_goff[d] -= ex;  // from here on relative to the tile's first element
+            }
         }
         __syncthreads();
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            if (rank[k] == 0xffffffffu) continue;
-            const uint32_t d = (key[k] >> shift) & 0xffu;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if (l0 + k * 64 >= tile_n) continue;
+            const uint32_t d = (key[k] >> shift) & (NB - 1u);
             const uint32_t p = s_dstart[d] + s_cnt[w][d] + rank[k];
             s_keys[p] = key[k];
             s_vals[p] = val[k];
         }
         __syncthreads();
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            const int p = k * RS_THREADS + threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const uint32_t p = k * RS_THREADS + threadIdx.x;
             if (p < tile_n) {
                 const uint32_t kk = s_keys[p];
-                const uint32_t d = (kk >> shift) & 0xffu;
-                const uint32_t o = s_goff[d] + ((uint32_t)p - s_dstart[d]);
+                const uint32_t o = s_goff[(kk >> shift) & (NB - 1u)] + p;
                 keys_out[o] = kk;
                 vals_out[o] = s_vals[p];
             }
@@ -406,74 +527,88 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const uint32_t* __res
     }
 }
 
-template <typename V>
-__global__ __launch_bounds__(256) void k_rs_copy(const uint32_t* __restrict__ ki, const V* __restrict__ vi,
-                                                 int64_t n_host, const uint32_t* __restrict__ n_dev,
-                                                 uint32_t* __restrict__ ko, V* __restrict__ vo) {
-    const int64_t n = rs_n(n_host, n_dev);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        ko[i] = ki[i];
-        vo[i] = vi[i];
-    }
-}
-
+// A digit's counts per 512- or 2048-key tile, twice (counts and offsets), and
+// its total.
 size_t radix_ws_bytes(int64_t n) {
-    int64_t tiles = (n + RS_TILE - 1) / RS_TILE;
-    if (tiles < 1) tiles = 1;
+    const int64_t small = n < RS_SMALL_KEYS ? n : RS_SMALL_KEYS;
+    int64_t tiles = (n + RGS_RADIX_TILE - 1) / RGS_RADIX_TILE, ts = (small + 2 * RS_THREADS - 1) / (2 * RS_THREADS);
+    if (tiles < ts) tiles = ts;
+    if (tiles < 2) tiles = 2;
     size_t h = (size_t)256 * tiles * sizeof(uint32_t);
     return 2 * ((h + 255) & ~size_t(255)) + 256 * sizeof(uint32_t) + 512;
 }
 
-template <typename V>
+RadixWs radix_ws(void* ws, const RadixPlan& p) {
+    const size_t h = (size_t)256 * (p.tiles < 2 ? 2 : p.tiles) * sizeof(uint32_t), hpad = (h + 255) & ~size_t(255);
+    char* b = reinterpret_cast<char*>(ws);
+    return RadixWs{reinterpret_cast<uint32_t*>(b), reinterpret_cast<uint32_t*>(b + hpad),
+                   reinterpret_cast<uint32_t*>(b + 2 * hpad)};
+}
+
+template <typename VIN, typename V, int BITS, int ITEMS>
+static void radix_pass(const uint32_t* ki, const VIN* vi, uint32_t* ko, V* vo, int64_t n, const uint32_t* n_dev, int shift,
+                       const RadixPlan& p, bool hist_ready, const RadixWs& w, hipStream_t s) {
+    const unsigned grid = (unsigned)(n_dev && p.tiles > DEV_GRID ? DEV_GRID : p.tiles);
+    if (!hist_ready)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_hist<BITS, ITEMS>), dim3(grid), dim3(RS_THREADS), 0, s, ki, n, n_dev, shift,
+                           p.fold, w.a, w.b);
+    if (!p.fold)
+        hipLaunchKernelGGL(k_rs_colscan, dim3(1 << BITS), dim3(RS_THREADS), 0, s, n, n_dev, p.items, w.a, w.b, w.dtot);
+    if (p.fold)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_scatter<VIN, V, BITS, ITEMS, true>), dim3(grid), dim3(RS_THREADS), 0, s, ki,
+                           vi, n, n_dev, shift, w.a, w.b, w.dtot, ko, vo);
+    else if constexpr (ITEMS > 2)  // (512-key tiles are always few)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_scatter<VIN, V, BITS, ITEMS, false>), dim3(grid), dim3(RS_THREADS), 0, s, ki,
+                           vi, n, n_dev, shift, w.a, w.b, w.dtot, ko, vo);
+}
+
+template <typename VIN, typename V, int ITEMS>
+static void radix_pass_bits(int bits, const uint32_t* ki, const VIN* vi, uint32_t* ko, V* vo, int64_t n,
+                            const uint32_t* n_dev, int shift, const RadixPlan& p, bool hist_ready, const RadixWs& w,
+                            hipStream_t s) {
+    switch (bits) {
+        case 6: radix_pass<VIN, V, 6, ITEMS>(ki, vi, ko, vo, n, n_dev, shift, p, hist_ready, w, s); break;
+        case 7: radix_pass<VIN, V, 7, ITEMS>(ki, vi, ko, vo, n, n_dev, shift, p, hist_ready, w, s); break;
+        default: radix_pass<VIN, V, 8, ITEMS>(ki, vi, ko, vo, n, n_dev, shift, p, hist_ready, w, s); break;
+    }
+}
+
+// FIRST: the first pass reads 4-byte sources from the start of its value buffer
+// and its histogram is in ws already (the producer wrote it).
+template <typename V, bool FIRST>
 static rgs_status radix_sort_impl(uint32_t* keys, V* vals, uint32_t* keys_alt, V* vals_alt, int64_t n,
-                                  const uint32_t* n_dev, int bits, void* ws, hipStream_t s) {
-    if (n <= 0 || bits <= 0) return RGS_OK;
-    int64_t tiles = (n + RS_TILE - 1) / RS_TILE;
-    size_t h = (size_t)256 * tiles * sizeof(uint32_t);
-    size_t hpad = (h + 255) & ~size_t(255);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(ws);
-    uint32_t* offs = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + hpad);
-    uint32_t* dtot = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + 2 * hpad);  // [256]
-    int passes = (bits + 7) / 8;
-    const unsigned grid = (unsigned)(n_dev && tiles > DEV_GRID ? DEV_GRID : tiles);
-    uint32_t *ki = keys, *ko = keys_alt;
-    V *vi = vals, *vo = vals_alt;
-    for (int p = 0; p < passes; ++p) {
-        int shift = 8 * p;
-        hipLaunchKernelGGL(k_rs_hist, dim3(grid), dim3(RS_THREADS), 0, s, ki, n, n_dev, shift, hist,
-                           (int)tiles);
-        hipLaunchKernelGGL(k_rs_colscan, dim3(256), dim3(RS_THREADS), 0, s, hist, n, n_dev, (int)tiles, offs, dtot);
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_scatter<V>), dim3(grid), dim3(RS_THREADS), 0, s, ki, vi,
-                           n, n_dev, shift, offs, dtot, (int)tiles, ko, vo);
+                                  const uint32_t* n_dev, const RadixPlan& p, void* ws, hipStream_t s) {
+    if (n <= 0) return RGS_OK;
+    const RadixWs w = radix_ws(ws, p);
+    const bool odd = p.passes & 1;
+    uint32_t *ki = odd ? keys_alt : keys, *ko = odd ? keys : keys_alt;
+    V *vi = odd ? vals_alt : vals, *vo = odd ? vals : vals_alt;
+    int shift = 0;
+    for (int k = 0; k < p.passes; ++k) {
+        if (FIRST && k == 0) {
+            const uint32_t* v32 = reinterpret_cast<const uint32_t*>(vi);
+            if (p.items == 2) radix_pass_bits<uint32_t, V, 2>(p.bits[k], ki, v32, ko, vo, n, n_dev, shift, p, true, w, s);
+            else radix_pass_bits<uint32_t, V, 8>(p.bits[k], ki, v32, ko, vo, n, n_dev, shift, p, true, w, s);
+        } else {
+            if (p.items == 2) radix_pass_bits<V, V, 2>(p.bits[k], ki, vi, ko, vo, n, n_dev, shift, p, false, w, s);
+            else radix_pass_bits<V, V, 8>(p.bits[k], ki, vi, ko, vo, n, n_dev, shift, p, false, w, s);
+        }
         RGS_LAUNCH_CHECK();
+        shift += p.bits[k];
         uint32_t* tk = ki; ki = ko; ko = tk;
         V* tv = vi; vi = vo; vo = tv;
-    }
-    if (ki != keys) {
-        // odd number of passes: copy back (the elements in use only)
-        const int64_t g0 = (n + 255) / 256;
-        const unsigned g = (unsigned)(g0 > DEV_GRID * 8 ? DEV_GRID * 8 : g0);
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_copy<V>), dim3(g), dim3(256), 0, s, ki, vi, n, n_dev, keys, vals);
-        RGS_LAUNCH_CHECK();
     }
     return RGS_OK;
 }
 
-rgs_status radix_sort_u32_u64(uint32_t* keys, uint64_t* vals, uint32_t* keys_alt, uint64_t* vals_alt, int64_t n,
-                              int bits, void* ws, hipStream_t s) {
-    return radix_sort_impl<uint64_t>(keys, vals, keys_alt, vals_alt, n, nullptr, bits, ws, s);
-}
 rgs_status radix_sort_u32_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t n,
-                              int bits, void* ws, hipStream_t s) {
-    return radix_sort_impl<uint32_t>(keys, vals, keys_alt, vals_alt, n, nullptr, bits, ws, s);
+                              const uint32_t* n_dev, const RadixPlan& p, void* ws, hipStream_t s) {
+    return radix_sort_impl<uint32_t, false>(keys, vals, keys_alt, vals_alt, n, n_dev, p, ws, s);
 }
-rgs_status radix_sort_u32_u64_dev(uint32_t* keys, uint64_t* vals, uint32_t* keys_alt, uint64_t* vals_alt,
-                                  const uint32_t* n_dev, int64_t n_max, int bits, void* ws, hipStream_t s) {
-    return radix_sort_impl<uint64_t>(keys, vals, keys_alt, vals_alt, n_max, n_dev, bits, ws, s);
-}
-rgs_status radix_sort_u32_u32_dev(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                                  const uint32_t* n_dev, int64_t n_max, int bits, void* ws, hipStream_t s) {
-    return radix_sort_impl<uint32_t>(keys, vals, keys_alt, vals_alt, n_max, n_dev, bits, ws, s);
+
+rgs_status radix_sort_instances(uint32_t* keys, uint64_t* vals, uint32_t* keys_alt, uint64_t* vals_alt, int64_t n,
+                                const uint32_t* n_dev, const RadixPlan& p, void* ws, hipStream_t s) {
+    return radix_sort_impl<uint64_t, true>(keys, vals, keys_alt, vals_alt, n, n_dev, p, ws, s);
 }
 
 }  // namespace rgs

@@ -60,3 +60,68 @@ def test_sparse_projection_equals_direct(rast, D):
     for k in raster.PARAM_KEYS:
         assert torch.equal(ga[k], gb[k]), k
         assert torch.count_nonzero(ga[k]) > 0, k
+
+
+@pytest.mark.parametrize("n,W,H,L,mu,views,sync", [
+    (1, 40, 24, 0, -1.0, 1, True),          # one pair, a single 6-bit pass (odd: the emission writes to the alt buffers)
+    (300, 16, 16, 0, -3.0, 1, True),        # one tile: no key bit at all
+    (5000, 256, 256, 2, -4.0, 1, False),    # 512-key tiles, emission of 256 instances per block
+    (30000, 256, 256, 2, -3.6, 1, True),    # beyond 64K instances: 2048-key tiles, still folded
+    (30000, 320, 200, 3, -3.0, 1, False),   # around the fold's 262144 instances
+    (40000, 333, 201, 3, -3.0, 1, True),    # beyond it
+    (20000, 3840, 2160, 5, -3.4, 1, True),  # 20 key bits, three passes; rectangles without a descriptor
+    (20000, 333, 201, 2, -4.0, 3, True),    # a fifth, view pass in the depth order
+    (64, 1600, 1060, 3, 0.0, 1, True),      # a few Gaussians of thousands of tiles each
+])
+def test_instance_lists_are_the_sorted_emission(n, W, H, L, mu, views, sync):
+    """Pairs in (view, depth, gid) order, offsets their running sum, instances a
+    stable sort by key of the emission, each pair's instances the tiles of its
+    rectangle times the ranks of its cells, without repetition."""
+    r = raster.Rasterizer()
+    p = raster.to_device(scenes.scene_uniform(n, seed=n, D=0, mu_s=mu))
+    kd = r.kd_partition(p, L)
+    cams = [scenes.orbit_camera(3.0, 0.3 + v, 0.3, W, H) for v in range(views)]
+    st = r.forward(p, kd, cams, 5e-5)
+    if not sync:
+        st = r.forward(p, kd, cams, 5e-5, no_sync=True)
+        assert st.overflow() == 0
+    b, V = st.bins, views
+    npair, ninst, nslot = (int(x) for x in b["counters"][:3].cpu())
+    count = st.proj["count"][: V * n].cpu().numpy().view(np.uint32).astype(np.int64)
+    depth = st.proj["depth"][: V * n].cpu().numpy()
+    vis = np.nonzero(count)[0]
+    order = vis[np.lexsort((vis, depth[vis], vis // n))]
+    assert npair == len(vis) and ninst == count.sum()
+    assert np.array_equal(b["pair_src"][:npair].cpu().numpy().view(np.uint32), order)
+    off = np.concatenate([[0], np.cumsum(count[order])])
+    assert np.array_equal(b["pair_off"][: npair + 1].cpu().numpy().view(np.uint32), off)
+    assert np.array_equal(b["pair_rank"].cpu().numpy()[order], np.arange(npair))
+    keys = b["keys"][:ninst].cpu().numpy().view(np.uint32).astype(np.int64)
+    vals = b["vals"][:ninst].cpu().numpy().view(np.uint64)
+    j, src = (vals & np.uint64(0xFFFFFFFF)).astype(np.int64), (vals >> np.uint64(32)).astype(np.int64)
+    assert np.array_equal(np.lexsort((j, keys)), np.arange(ninst))  # sorted by key, ties in emission order
+    assert np.array_equal(np.sort(j), np.arange(ninst))
+    pair = np.searchsorted(off, j, side="right") - 1
+    assert np.array_equal(order[pair], src)
+    # every pair's keys are distinct, its tiles inside its rectangle, its ranks those of its cells
+    K = 1 << L
+    assert len(np.unique(pair * (1 << 32) + keys)) == ninst
+    rec = st.proj["bin"][: 8 * V * n].view(V * n, 8).cpu().numpy().view(np.uint32)
+    rect = np.ascontiguousarray(rec[:, :2]).view(np.int16).astype(np.int64)
+    mask = np.ascontiguousarray(rec[:, 4:6]).view(np.uint64)[:, 0]
+    ranks = r.cell_ranks(kd, cams)
+    tx_n = (W + 15) // 16
+    per_view = tx_n * ((H + 15) // 16)
+    v = src // n
+    t = keys // K - v * per_view
+    assert np.all((t >= 0) & (t < per_view))
+    tx, ty = t % tx_n, t // tx_n
+    q = rect[src]
+    assert np.all((tx >= q[:, 0] >> 4) & (tx <= q[:, 1] >> 4) & (ty >= q[:, 2] >> 4) & (ty <= q[:, 3] >> 4))
+    cell = np.argsort(ranks, 1)[v, keys % K]
+    assert np.all((mask[src] >> cell.astype(np.uint64)) & np.uint64(1))
+    # slots: the runs of equal keys
+    start = np.nonzero(np.concatenate([[True], np.diff(keys) != 0]))[0]
+    assert nslot == len(start)
+    assert np.array_equal(b["slot_range"][: 2 * nslot].cpu().numpy().reshape(-1, 2),
+                          np.stack([start, np.append(start[1:], ninst)], 1))
