@@ -99,6 +99,46 @@ __device__ __forceinline__ bool box_hits(float mx, float my, float ca, float cb,
     return qmin <= tau + 0x1p-18f * far + 0x1p-20f * tau;
 }
 
+#define RGS_DPP(v, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (v)), (ctrl), 0xf, 0xf, false))
+
+// Lane mask of a comparison (the compare writes it to scalar registers).
+__device__ __forceinline__ uint64_t wmask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
+// 4x4 blocks of the pixel row band by .. by + 3, from column bx on, that the
+// footprint can reach: bit c = block column c < 2.  The band's
+// span of columns as in row_span, with the hardware's reciprocal and square
+// root; the enlargement of tau and the pads at the ends are four times those of
+// row_span, above the error of both the per-pixel test and these, so a block
+// is only dropped when none of its pixels can contribute.
+__device__ __forceinline__ uint32_t block_row_mask(float4 a, float4 b, uint2 rr, int bx, int by, bool rect_only) {
+    const int x_lo = (int)(int16_t)(rr.x & 0xffffu), x_hi = (int)(int16_t)(rr.x >> 16);
+    const int y_lo = (int)(int16_t)(rr.y & 0xffffu), y_hi = (int)(int16_t)(rr.y >> 16);
+    const int y0 = max(by, y_lo), y1 = min(by + 3, y_hi);
+    float lo = (float)x_lo, hi = (float)x_hi;
+    if (!rect_only) {
+        const float mx = a.x, my = a.y, ca = a.z, k = a.w, e = b.x, tau = b.z;
+        const float ica = __builtin_amdgcn_rcpf(ca), ie = __builtin_amdgcn_rcpf(e), q = (k * k) * ca;
+        const float rk = __builtin_amdgcn_sqrtf(fmaf(q, ie, 1.0f));
+        const float taup = fmaf(tau, 0x1p-16f * (1.0f + rk), tau);
+        const float dyr = -(k * __builtin_amdgcn_sqrtf((ca * taup) * (ie * __builtin_amdgcn_rcpf(e + q))));
+        const float ly = ((float)y0 + 0.5f) - my, hy = ((float)y1 + 0.5f) - my;
+        const float dR = fminf(fmaxf(dyr, ly), hy), dL = fminf(fmaxf(-dyr, ly), hy);
+        const float xr = mx + (__builtin_amdgcn_sqrtf(fmaxf(taup - e * (dR * dR), 0.0f) * ica) - k * dR);
+        const float xl = mx - (__builtin_amdgcn_sqrtf(fmaxf(taup - e * (dL * dL), 0.0f) * ica) + k * dL);
+        const float pr = 0x1p-4f + 0x1p-14f * (fabsf(mx) + fabsf(xr - mx));
+        const float pl = 0x1p-4f + 0x1p-14f * (fabsf(mx) + fabsf(xl - mx));
+        // an end that is not finite leaves the rectangle's bound
+        if (fabsf(xl) < INFINITY && fabsf(xr) < INFINITY && fabsf(dyr) < INFINITY) {
+            lo = fmaxf((xl - pl) - 0.5f, lo);
+            hi = fminf((xr + pr) - 0.5f, hi);
+        }
+    }
+    // pixels lo .. hi (rounded outwards) to block columns
+    const int c0 = max(((int)floorf(lo) - bx) >> 2, 0), c1 = min(((int)floorf(hi) - bx) >> 2, 1);
+    if (y0 > y1 || !(lo <= hi) || c0 > c1) return 0u;
+    return (2u << c1) - (1u << c0);
+}
+
 // Forward: one 256-thread block per tile, walking the tile's slots (one per
 // cell that has instances there) in the view's merge order; wave w owns the
 // 8x8 quadrant (w & 1, w >> 1) of the tile, one pixel per lane.  Each pixel
@@ -111,13 +151,37 @@ __device__ __forceinline__ bool box_hits(float mx, float my, float ca, float cb,
 // (their partial stays C = 0, T = 1, last = 0).  Records are staged 256 at a
 // time in LDS, each with the quadrant mask of its rectangle so that a wave
 // skips Gaussians that cannot touch its quadrant with a scalar branch.
+//
+// A tile's list is a serial chain, and a wave alone on its SIMD issues an
+// instruction about every eight clocks (400 clocks per instance here), so the
+// tiles with the longest lists were the kernel's time for small and middle
+// views (300k Gaussians at 997x663: all other tiles done in 95 us, the last at
+// 246).  The RF_HEAVY first tiles of the launch order are therefore given to
+// four blocks each, one per quadrant, whose waves own 4x4 pixels and take four
+// instances at a time: lane = 4 pixel + instance for the sigmas, the
+// transmittances passed along the quad by DPP, lane = 4 pixel + channel for the
+// colours, which are added instance by instance.  Every value is formed by the
+// same operations in the same order as with a pixel per lane, so the results
+// are the same bits and the choice is free.  A wave's list holds only the
+// records whose ellipse reaches its 4x4 block.  This costs twice the
+// instructions per (pixel, instance) pair, so it is not for every tile: with
+// all tiles so, 300k Gaussians take 120 us and 20k at 256x256 30, but 1M at
+// 1920x1080 293 instead of 212 and 16M at 3840x2160 990 instead of 550.  256
+// tiles are the 1024 blocks that the chip starts with (4 per CU).  Measured
+// in us, before / with the first 128 / 256 / 512 tiles: 20k at 256x256 66 /
+// 28 / 28 / 28; 150k at 1237x823 165 / 123 / 127 / more; 300k at 997x663
+// 228 / 128 / 128 / more; 1M at 1600x1060 312 / 300 / 228; 1M at 1920x1080 (no long
+// tiles) 212 / 222 / 218; 16M at 3840x2160 551 / 523 / 519.
+// 64 registers keep 8 waves per SIMD (72 and 7 waves: 246 at 1920x1080).
+static constexpr uint32_t RF_HEAVY = 256;
+
 template <bool STATS>
-__global__ __launch_bounds__(256) void k_render_fwd(const float* __restrict__ rec,
+__global__ __launch_bounds__(256, 8) void k_render_fwd(const float* __restrict__ rec,
                                                     const uint64_t* __restrict__ vals,
                                                     const uint32_t* __restrict__ slot_key,
                                                     const uint32_t* __restrict__ slot_range,
                                                     const uint32_t* __restrict__ tile_slot,
-                                                    const uint32_t* __restrict__ tile_order,
+                                                    const uint32_t* __restrict__ tile_order, uint32_t n_heavy,
                                                     const ViewTable* __restrict__ vt, const float* __restrict__ box_lo,
                                                     const float* __restrict__ box_hi, float eps_T,
                                                     float* __restrict__ outC, float* __restrict__ outT,
@@ -125,12 +189,14 @@ __global__ __launch_bounds__(256) void k_render_fwd(const float* __restrict__ re
                                                     unsigned long long* __restrict__ stats,
                                                     float* __restrict__ image, float* __restrict__ T_final) {
     constexpr int NB = 256;
-    __shared__ float4 sA[NB], sB[NB], sCl[NB];
+    // record NB never contributes (tau < 0): it fills a list's last group of four
+    __shared__ float4 sA[NB + 1], sB[NB + 1], sCl[NB + 1];
     __shared__ uint32_t sM[NB];
-    __shared__ uint2 sR[NB];
-    __shared__ uint32_t s_alive[4];
-    __shared__ uint32_t s_live[4];
-    const uint32_t gt = tile_order[blockIdx.x];
+    __shared__ uint2 sR[STATS ? NB : 1];
+    __shared__ uint32_t s_flag[2][4];
+    __shared__ __align__(8) uint16_t s_list[4][NB + 8];
+    const bool heavy = blockIdx.x < 4 * n_heavy;
+    const uint32_t gt = tile_order[heavy ? blockIdx.x >> 2 : blockIdx.x - 3 * n_heavy];
     const uint32_t s0 = tile_slot[gt], s1 = tile_slot[gt + 1];
     if (s0 >= s1 && !image) return;
     const int L = vt->L, K = 1 << L;
@@ -139,142 +205,329 @@ __global__ __launch_bounds__(256) void k_render_fwd(const float* __restrict__ re
     const ViewParams& V = vt->v[v];
     const uint32_t lt = gt - V.tile_offset;
     const int tx = (int)(lt % (uint32_t)V.tiles_x), ty = (int)(lt / (uint32_t)V.tiles_x);
-    const int lx = (w & 1) * 8 + (lane & 7), ly = (w >> 1) * 8 + (lane >> 3);
-    const int px = tx * 16 + lx, py = ty * 16 + ly;
-    // merged image (image != null): the fold of Eq. 5 over the tile's slots in
-    // their order, as the merge does it from the stored partials
-    float M0 = 0.f, M1 = 0.f, M2 = 0.f;
-    const float fxp = (float)px + 0.5f;
-    const float dxp = (fxp - V.cx) / V.fx, dyp = ((float)py + 0.5f - V.cy) / V.fy;
-    const float D0 = (V.R[0] * dxp + V.R[3] * dyp) + V.R[6];
-    const float D1 = (V.R[1] * dxp + V.R[4] * dyp) + V.R[7];
-    const float D2 = (V.R[2] * dxp + V.R[5] * dyp) + V.R[8];
     const float o0 = V.o[0], o1 = V.o[1], o2 = V.o[2];
-    // a stopped (or off-image) pixel samples row +inf: d^2 = inf fails every test
-    bool live = px < V.W && py < V.H;
-    float P = 1.0f;
     uint32_t n_eval = 0u, n_con = 0u;
-    const uint32_t qbit = 1u << (w + 1);
-    const int p = ly * 16 + lx;
 
-    for (uint32_t slot = s0; slot < s1; ++slot) {
-        if (slot > s0) {
-            // once every pixel of the tile has stopped, the remaining slots are
-            // neutral: written without staging a record (P only decreases, so
-            // the tile stays stopped)
-            const uint64_t lv = __ballot(live);
-            if (lane == 0) s_live[w] = lv != 0ull ? 1u : 0u;
-            __syncthreads();
-            if ((s_live[0] | s_live[1] | s_live[2] | s_live[3]) == 0u) {
-                for (uint32_t sn = slot; sn < s1; ++sn) {
-                    float* on = outC + (size_t)sn * 768;
-                    on[p] = 0.f;
-                    on[256 + p] = 0.f;
-                    on[512 + p] = 0.f;
-                    outT[(size_t)sn * 256 + p] = 1.f;
-                    outLast[(size_t)sn * 256 + p] = 0u;
+    if (heavy) {
+        const int quadr = (int)(blockIdx.x & 3u), inst = lane & 3, pix = lane >> 2;
+        const int qlx = (quadr & 1) * 8, qly = (quadr >> 1) * 8;                       // the block's quadrant in the tile
+        const int lx = qlx + (w & 1) * 4 + (pix & 3), ly = qly + (w >> 1) * 4 + (pix >> 2);
+        const int px = tx * 16 + lx, py = ty * 16 + ly, p = ly * 16 + lx;
+        const float fxp = (float)px + 0.5f, fyp = (float)py + 0.5f;
+        const float dxp = (fxp - V.cx) / V.fx, dyp = (fyp - V.cy) / V.fy;
+        const float D0 = (V.R[0] * dxp + V.R[3] * dyp) + V.R[6];
+        const float D1 = (V.R[1] * dxp + V.R[4] * dyp) + V.R[7];
+        const float D2 = (V.R[2] * dxp + V.R[5] * dyp) + V.R[8];
+        const bool on_image = px < V.W && py < V.H;
+        bool live = on_image;
+        float P = 1.0f, M = 0.f;  // M: the merged colour's channel `inst`
+        if (tid == 0) {
+            sA[NB] = sCl[NB] = make_float4(0.f, 0.f, 0.f, 0.f);
+            sB[NB] = make_float4(0.f, 0.f, -1.f, 0.f);
+        }
+        // the stream of the tile's instances (its slots are contiguous in the list):
+        // the source of the next batch's record is loaded ahead
+        uint32_t src = 0, tile_end = 0;
+        const uint32_t* vhi = reinterpret_cast<const uint32_t*>(vals) + 1;  // high words: the sources
+        auto next_src = [&](uint32_t at) {  // (past the tile's end: its last instance)
+            const uint32_t i = at + (uint32_t)tid;
+            src = vhi[2 * (size_t)(i < tile_end ? i : tile_end - 1u)];
+        };
+        if (s0 < s1) {
+            tile_end = slot_range[2 * (s1 - 1) + 1];
+            next_src(slot_range[2 * s0]);
+        }
+        int par = 0;  // parity of the batch (its flags are read while the next one's are written)
+        for (uint32_t slot = s0; slot < s1; ++slot) {
+            const uint32_t key = slot_key[slot];
+            const uint32_t begin = slot_range[2 * slot], end = slot_range[2 * slot + 1];
+            const int cell = V.cell_of_rank[key & ((1u << L) - 1u)];
+            const float blo0 = box_lo[cell], blo1 = box_lo[K + cell], blo2 = box_lo[2 * K + cell];
+            const float bhi0 = box_hi[cell], bhi1 = box_hi[K + cell], bhi2 = box_hi[2 * K + cell];
+            // a pixel that has stopped (or is off the image) takes no contribution
+            const float thr = live ? eps_T / P : INFINITY;
+            float T = 1.0f, C = 0.f;  // C: channel `inst`
+            uint32_t last = 0u;
+            bool any_alive = false;
+            for (uint32_t base = begin;;) {
+                const int nb = (int)((end - base) < (uint32_t)NB ? (end - base) : (uint32_t)NB);
+                const uint32_t next = base + (uint32_t)nb;  // the next batch of this slot, or the next slot's first
+                const float4* rp = reinterpret_cast<const float4*>(rec) + 4 * (size_t)src;
+                const float4 ra = rp[0], rb = rp[1], rc = rp[2];
+                const float2 rr = *reinterpret_cast<const float2*>(rp + 3);
+                sA[tid] = ra;
+                sB[tid] = rb;
+                sCl[tid] = make_float4(rc.x, rc.y, rc.z, __uint_as_float(base - begin + (uint32_t)tid + 1u));
+                const uint2 rct = make_uint2(__float_as_uint(rr.x), __float_as_uint(rr.y));
+                if (STATS) sR[tid] = rct;
+                uint32_t m = 0u;
+                if (tid < nb) {
+                    const int bx = tx * 16 + qlx, by = ty * 16 + qly;
+                    m = block_row_mask(ra, rb, rct, bx, by, STATS) | (block_row_mask(ra, rb, rct, bx, by + 4, STATS) << 2);
+                    m |= (__float_as_uint(rc.w) & 1u) ? 0u : 16u;  // its footprint reaches several cells
+                }
+                sM[tid] = m;
+                const uint64_t am = wmask(!(T < thr));
+                // colours are >= 0: all finite if their sum is
+                const uint64_t odd_m = wmask(tid < nb && !((rc.x + rc.y) + rc.z < INFINITY));
+                if (lane == 0) s_flag[par][w] = (am != 0ull ? 1u : 0u) | (odd_m != 0ull ? 2u : 0u);
+                next_src(next);
+                __syncthreads();
+                const uint32_t fl = s_flag[par][0] | s_flag[par][1] | s_flag[par][2] | s_flag[par][3];
+                par ^= 1;
+                any_alive = (fl & 1u) != 0u;
+                if (!any_alive) break;
+                if (am != 0ull) {
+                    int cnt = 0;
+#pragma unroll
+                    for (int k = 0; k < NB / 64; ++k) {
+                        const uint32_t mk = sM[k * 64 + lane];
+                        const bool hit = (mk >> w) & 1u;
+                        const uint64_t rel = wmask(hit);
+                        const int at = cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rel >> 32),
+                                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)rel, 0u));
+                        if (hit) s_list[w][at] = (uint16_t)(((k * 64 + lane) << 4) | (mk >> 4));
+                        cnt += (int)__popcll(rel);
+                    }
+                    if (lane < 8) s_list[w][cnt + lane] = (uint16_t)(NB << 4);
+                    __builtin_amdgcn_wave_barrier();
+                    uint32_t en = s_list[w][inst];
+                    for (int g = 0; g < cnt; g += 4) {
+                        const uint32_t ad = en & 0xfff0u;
+                        const bool mul = en & 1u;
+                        en = s_list[w][g + 4 + inst];
+                        const float4 ac = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(sA) + ad);
+                        const float4 bc = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(sB) + ad);
+                        const uint32_t idx = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(sCl) + ad + 12);
+                        // channel `inst` of the four instances' colours (the index for lane 3, unused)
+                        float cv[4];
+#define RGS_QUAD(i) (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ad, (i) * 0x55, 0xf, 0xf, false)
+                        cv[0] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(sCl) + RGS_QUAD(0) + 4 * inst);
+                        cv[1] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(sCl) + RGS_QUAD(1) + 4 * inst);
+                        cv[2] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(sCl) + RGS_QUAD(2) + 4 * inst);
+                        cv[3] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(sCl) + RGS_QUAD(3) + 4 * inst);
+#undef RGS_QUAD
+                        const float dx = fxp - ac.x, dy = fyp - ac.y;
+                        const float u = fmaf(ac.w, dy, dx);  // d^2 = ca u^2 + e dy^2
+                        const float d2 = fmaf(bc.x * dy, dy, (ac.z * u) * u);
+                        bool con = d2 <= bc.z;
+                        if (wmask(mul) != 0ull) {  // the indicator of Eq. 6, where a footprint reaches several cells
+                            const float x0 = fmaf(bc.w, D0, o0), x1 = fmaf(bc.w, D1, o1), x2 = fmaf(bc.w, D2, o2);
+                            const bool in = (blo0 <= x0) && (x0 < bhi0) && (blo1 <= x1) && (x1 < bhi1) && (blo2 <= x2) &&
+                                            (x2 < bhi2);
+                            con = con && (in || !mul);
+                        }
+                        const float G = __builtin_amdgcn_exp2f(d2 * -0.72134752044448170368f);  // exp(-d^2/2)
+                        const float sg = con ? fminf(0.99f, bc.y * G) : 0.0f;
+                        const float a = 1.0f - sg;
+                        // the transmittance after each instance of the quad, one product after another
+                        // (DPP reads are made by all lanes, before any selection)
+                        const float t0 = T * a;
+                        const float t1 = RGS_DPP(t0, 0x00) * a;
+                        const float t2 = RGS_DPP(t1, 0x55) * a;
+                        const float t3 = RGS_DPP(t2, 0xaa) * a;
+                        const float Ta = inst < 2 ? (inst == 0 ? t0 : t1) : (inst == 2 ? t2 : t3);
+                        const float sb = RGS_DPP(Ta, 0x90);    // quad_perm [0,0,1,2]
+                        const float Tb = inst >= 1 ? sb : T;   // ... and before it
+                        const bool on = !(Tb < thr);           // included unless the pixel stopped before it
+                        if (STATS) {
+                            // pairs the method must test: pixel inside the Gaussian's rectangle, not yet stopped
+                            const uint2 rr2 = sR[ad < (uint32_t)(NB << 4) ? ad >> 4 : 0u];
+                            const bool inr = px >= (int)(int16_t)(rr2.x & 0xffffu) && px <= (int)(int16_t)(rr2.x >> 16) &&
+                                             py >= (int)(int16_t)(rr2.y & 0xffffu) && py <= (int)(int16_t)(rr2.y >> 16);
+                            n_eval += on && inr && ad < (uint32_t)(NB << 4) ? 1u : 0u;
+                            n_con += on && con ? 1u : 0u;
+                        }
+                        const float wgt = on && con ? sg * Tb : -0.0f;  // (a weight has no sign)
+                        last = on && con ? idx : last;
+                        const float w0 = RGS_DPP(wgt, 0x00), w1 = RGS_DPP(wgt, 0x55), w2 = RGS_DPP(wgt, 0xaa),
+                                    w3 = RGS_DPP(wgt, 0xff);
+                        if (__builtin_expect((fl & 2u) != 0u, 0)) {
+                            // a colour of the batch is not finite: what is not included leaves C as it is
+                            C = (int)__float_as_uint(w0) >= 0 ? fmaf(w0, cv[0], C) : C;
+                            C = (int)__float_as_uint(w1) >= 0 ? fmaf(w1, cv[1], C) : C;
+                            C = (int)__float_as_uint(w2) >= 0 ? fmaf(w2, cv[2], C) : C;
+                            C = (int)__float_as_uint(w3) >= 0 ? fmaf(w3, cv[3], C) : C;
+                        } else {
+                            C = fmaf(w3, cv[3], fmaf(w2, cv[2], fmaf(w1, cv[1], fmaf(w0, cv[0], C))));
+                        }
+                        // the transmittance after the last included instance: the least of the quad's
+                        // (not negative: ordered like their bits)
+                        uint32_t Tn = __float_as_uint(on ? Ta : T);
+                        Tn = min(Tn, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)Tn, 0xb1, 0xf, 0xf, false));
+                        Tn = min(Tn, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)Tn, 0x4e, 0xf, 0xf, false));
+                        T = __uint_as_float(Tn);
+                        if (wmask(!(T < thr)) == 0ull) break;
+                    }
+                }
+                __syncthreads();
+                if (next >= end) break;
+                base = next;
+            }
+            last = max(last, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)last, 0xb1, 0xf, 0xf, false));
+            last = max(last, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)last, 0x4e, 0xf, 0xf, false));
+            {  // lane 4 pixel + c writes component c (C, then T)
+                float* o = inst < 3 ? outC + (size_t)slot * 768 + 256 * inst : outT + (size_t)slot * 256;
+                o[p] = inst < 3 ? C : T;
+                if (inst == 0) outLast[(size_t)slot * 256 + p] = last;
+            }
+            // the walk stopped in this cell: every later cell is neutral here
+            if (T < thr) live = false;
+            M = fmaf(P, C, M);
+            P *= T;
+            if (!any_alive) {
+                // every pixel of the quadrant has stopped: its share of the remaining
+                // slots is neutral, written without staging a record
+                for (uint32_t sn = slot + 1; sn < s1; ++sn) {
+                    float* o = inst < 3 ? outC + (size_t)sn * 768 + 256 * inst : outT + (size_t)sn * 256;
+                    o[p] = inst < 3 ? 0.f : 1.f;
+                    if (inst == 0) outLast[(size_t)sn * 256 + p] = 0u;
                 }
                 break;
             }
         }
-        const uint32_t key = slot_key[slot];
-        const int cell = V.cell_of_rank[key & ((1u << L) - 1u)];
-        const uint32_t begin = slot_range[2 * slot], end = slot_range[2 * slot + 1];
-        const float blo0 = box_lo[cell], blo1 = box_lo[K + cell], blo2 = box_lo[2 * K + cell];
-        const float bhi0 = box_hi[cell], bhi1 = box_hi[K + cell], bhi2 = box_hi[2 * K + cell];
-        // stop once P T < eps_T, i.e. T < eps_T / P (>= eps_T: T stays normal)
-        const float thr = live ? eps_T / P : 0.0f;
-        float fyp = live ? (float)py + 0.5f : INFINITY;
-        float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
-        uint32_t last = 0u;
-        for (uint32_t base = begin; base < end; base += NB) {
-            const uint64_t alive = __ballot(fyp != INFINITY);
-            if (lane == 0) s_alive[w] = alive != 0ull ? 1u : 0u;
-            const uint32_t idx = base + tid;
-            if (idx < end) {
-                const uint32_t src = (uint32_t)(vals[idx] >> 32);
-                const float4* rp = reinterpret_cast<const float4*>(rec + (size_t)src * RGS_REC_FLOATS);
-                const float4 a = rp[0];
-                const float4 b = rp[1], cl = rp[2], r4 = rp[3];
-                const uint2 rr = make_uint2(__float_as_uint(r4.x), __float_as_uint(r4.y));
-                sM[tid] = (quad_mask(rr, tx, ty) << 1) | (__float_as_uint(cl.w) & 1u);
-                sA[tid] = a;
-                sB[tid] = b;
-                sCl[tid] = cl;
-                if (STATS) sR[tid] = rr;
-            }
-            __syncthreads();
-            if ((s_alive[0] | s_alive[1] | s_alive[2] | s_alive[3]) == 0u) break;
-            const int nb = (int)((end - base) < (uint32_t)NB ? (end - base) : (uint32_t)NB);
-            if (alive != 0ull) {
-                // Gaussians of this batch whose footprint can reach the wave's
-                // quadrant, walked in order (other waves hide the LDS latency);
-                // the wave leaves the batch once all its pixels have stopped
-#pragma unroll
-                for (int k = 0; k < NB / 64; ++k) {
-                    if (k > 0 && __ballot(fyp != INFINITY) == 0ull) break;
-                    const int tl = k * 64 + lane;
-                    const uint32_t mk = tl < nb ? sM[tl] : 0u;
-                    uint64_t rel = __ballot((mk & qbit) != 0u);
-                    const uint64_t inside = __ballot((mk & 1u) != 0u);  // footprint in one cell: no indicator test
-                    while (rel) {
-                        const int bit = (int)__builtin_ctzll(rel);
-                        const int tc = k * 64 + bit;
-                        rel &= rel - 1ull;
-                        const float4 ac = sA[tc], bc = sB[tc];
-                        const float dx = fxp - ac.x, dy = fyp - ac.y;
-                        const float u = fmaf(ac.w, dy, dx);  // d^2 = ca u^2 + e dy^2
-                        const float d2 = fmaf(bc.x * dy, dy, (ac.z * u) * u);
-                        if (STATS && fyp != INFINITY) {
-                            // pairs the method must test: pixel inside the Gaussian's rectangle
-                            const uint2 rr = sR[tc];
-                            const bool inr = px >= (int)(int16_t)(rr.x & 0xffffu) && px <= (int)(int16_t)(rr.x >> 16) &&
-                                             py >= (int)(int16_t)(rr.y & 0xffffu) && py <= (int)(int16_t)(rr.y >> 16);
-                            n_eval += inr ? 1u : 0u;
-                        }
-                        if (!(d2 <= bc.z)) continue;
-                        const float4 cl = sCl[tc];
-                        if (!((inside >> bit) & 1ull)) {
-                            const float x0 = fmaf(bc.w, D0, o0), x1 = fmaf(bc.w, D1, o1), x2 = fmaf(bc.w, D2, o2);
-                            const bool in = (blo0 <= x0) && (x0 < bhi0) && (blo1 <= x1) && (x1 < bhi1) && (blo2 <= x2) &&
-                                            (x2 < bhi2);
-                            if (!in) continue;
-                        }
-                        if (STATS) ++n_con;
-                        const float G = __builtin_amdgcn_exp2f(d2 * -0.72134752044448170368f);  // exp(-d^2/2)
-                        const float sg = fminf(0.99f, bc.y * G);
-                        const float wgt = sg * T;
-                        C0 = fmaf(wgt, cl.x, C0);
-                        C1 = fmaf(wgt, cl.y, C1);
-                        C2 = fmaf(wgt, cl.z, C2);
-                        T = T * (1.0f - sg);
-                        last = base - begin + (uint32_t)tc + 1u;
-                        if (T < thr) fyp = INFINITY;
+        if (image && on_image) {
+            const size_t HW = (size_t)V.W * V.H, at = (size_t)py * V.W + px;
+            const float bgc = inst == 0 ? V.bg[0] : (inst == 1 ? V.bg[1] : V.bg[2]);
+            float* o = inst < 3 ? image + 3 * (size_t)V.pix_offset + HW * inst : T_final + V.pix_offset;
+            o[at] = inst < 3 ? fmaf(P, bgc, M) : P;
+        }
+    } else {
+        const int lx = (w & 1) * 8 + (lane & 7), ly = (w >> 1) * 8 + (lane >> 3);
+        const int px = tx * 16 + lx, py = ty * 16 + ly;
+        // merged image (image != null): the fold of Eq. 5 over the tile's slots in
+        // their order, as the merge does it from the stored partials
+        float M0 = 0.f, M1 = 0.f, M2 = 0.f;
+        const float fxp = (float)px + 0.5f;
+        const float dxp = (fxp - V.cx) / V.fx, dyp = ((float)py + 0.5f - V.cy) / V.fy;
+        const float D0 = (V.R[0] * dxp + V.R[3] * dyp) + V.R[6];
+        const float D1 = (V.R[1] * dxp + V.R[4] * dyp) + V.R[7];
+        const float D2 = (V.R[2] * dxp + V.R[5] * dyp) + V.R[8];
+        // a stopped (or off-image) pixel samples row +inf: d^2 = inf fails every test
+        bool live = px < V.W && py < V.H;
+        float P = 1.0f;
+        const uint32_t qbit = 1u << (w + 1);
+        const int p = ly * 16 + lx;
+
+        for (uint32_t slot = s0; slot < s1; ++slot) {
+            if (slot > s0) {
+                // once every pixel of the tile has stopped, the remaining slots are
+                // neutral: written without staging a record (P only decreases, so
+                // the tile stays stopped)
+                const uint64_t lv = __ballot(live);
+                if (lane == 0) s_flag[0][w] = lv != 0ull ? 1u : 0u;
+                __syncthreads();
+                if ((s_flag[0][0] | s_flag[0][1] | s_flag[0][2] | s_flag[0][3]) == 0u) {
+                    for (uint32_t sn = slot; sn < s1; ++sn) {
+                        float* on = outC + (size_t)sn * 768;
+                        on[p] = 0.f;
+                        on[256 + p] = 0.f;
+                        on[512 + p] = 0.f;
+                        outT[(size_t)sn * 256 + p] = 1.f;
+                        outLast[(size_t)sn * 256 + p] = 0u;
                     }
+                    break;
                 }
             }
-            __syncthreads();
+            const uint32_t key = slot_key[slot];
+            const int cell = V.cell_of_rank[key & ((1u << L) - 1u)];
+            const uint32_t begin = slot_range[2 * slot], end = slot_range[2 * slot + 1];
+            const float blo0 = box_lo[cell], blo1 = box_lo[K + cell], blo2 = box_lo[2 * K + cell];
+            const float bhi0 = box_hi[cell], bhi1 = box_hi[K + cell], bhi2 = box_hi[2 * K + cell];
+            // stop once P T < eps_T, i.e. T < eps_T / P (>= eps_T: T stays normal)
+            const float thr = live ? eps_T / P : 0.0f;
+            float fyp = live ? (float)py + 0.5f : INFINITY;
+            float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+            uint32_t last = 0u;
+            for (uint32_t base = begin; base < end; base += NB) {
+                const uint64_t alive = __ballot(fyp != INFINITY);
+                if (lane == 0) s_flag[1][w] = alive != 0ull ? 1u : 0u;
+                const uint32_t idx = base + tid;
+                if (idx < end) {
+                    const uint32_t src = (uint32_t)(vals[idx] >> 32);
+                    const float4* rp = reinterpret_cast<const float4*>(rec + (size_t)src * RGS_REC_FLOATS);
+                    const float4 a = rp[0];
+                    const float4 b = rp[1], cl = rp[2], r4 = rp[3];
+                    const uint2 rr = make_uint2(__float_as_uint(r4.x), __float_as_uint(r4.y));
+                    sM[tid] = (quad_mask(rr, tx, ty) << 1) | (__float_as_uint(cl.w) & 1u);
+                    sA[tid] = a;
+                    sB[tid] = b;
+                    sCl[tid] = cl;
+                    if (STATS) sR[tid] = rr;
+                }
+                __syncthreads();
+                if ((s_flag[1][0] | s_flag[1][1] | s_flag[1][2] | s_flag[1][3]) == 0u) break;
+                const int nb = (int)((end - base) < (uint32_t)NB ? (end - base) : (uint32_t)NB);
+                if (alive != 0ull) {
+                    // Gaussians of this batch whose footprint can reach the wave's
+                    // quadrant, walked in order (other waves hide the LDS latency);
+                    // the wave leaves the batch once all its pixels have stopped
+#pragma unroll
+                    for (int k = 0; k < NB / 64; ++k) {
+                        if (k > 0 && __ballot(fyp != INFINITY) == 0ull) break;
+                        const int tl = k * 64 + lane;
+                        const uint32_t mk = tl < nb ? sM[tl] : 0u;
+                        uint64_t rel = __ballot((mk & qbit) != 0u);
+                        const uint64_t inside = __ballot((mk & 1u) != 0u);  // footprint in one cell: no indicator test
+                        while (rel) {
+                            const int bit = (int)__builtin_ctzll(rel);
+                            const int tc = k * 64 + bit;
+                            rel &= rel - 1ull;
+                            const float4 ac = sA[tc], bc = sB[tc];
+                            const float dx = fxp - ac.x, dy = fyp - ac.y;
+                            const float u = fmaf(ac.w, dy, dx);  // d^2 = ca u^2 + e dy^2
+                            const float d2 = fmaf(bc.x * dy, dy, (ac.z * u) * u);
+                            if (STATS && fyp != INFINITY) {
+                                // pairs the method must test: pixel inside the Gaussian's rectangle
+                                const uint2 rr = sR[tc];
+                                const bool inr = px >= (int)(int16_t)(rr.x & 0xffffu) && px <= (int)(int16_t)(rr.x >> 16) &&
+                                                 py >= (int)(int16_t)(rr.y & 0xffffu) && py <= (int)(int16_t)(rr.y >> 16);
+                                n_eval += inr ? 1u : 0u;
+                            }
+                            if (!(d2 <= bc.z)) continue;
+                            const float4 cl = sCl[tc];
+                            if (!((inside >> bit) & 1ull)) {
+                                const float x0 = fmaf(bc.w, D0, o0), x1 = fmaf(bc.w, D1, o1), x2 = fmaf(bc.w, D2, o2);
+                                const bool in = (blo0 <= x0) && (x0 < bhi0) && (blo1 <= x1) && (x1 < bhi1) && (blo2 <= x2) &&
+                                                (x2 < bhi2);
+                                if (!in) continue;
+                            }
+                            if (STATS) ++n_con;
+                            const float G = __builtin_amdgcn_exp2f(d2 * -0.72134752044448170368f);  // exp(-d^2/2)
+                            const float sg = fminf(0.99f, bc.y * G);
+                            const float wgt = sg * T;
+                            C0 = fmaf(wgt, cl.x, C0);
+                            C1 = fmaf(wgt, cl.y, C1);
+                            C2 = fmaf(wgt, cl.z, C2);
+                            T = T * (1.0f - sg);
+                            last = base - begin + (uint32_t)tc + 1u;
+                            if (T < thr) fyp = INFINITY;
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+            float* oc = outC + (size_t)slot * 768;
+            oc[p] = C0;
+            oc[256 + p] = C1;
+            oc[512 + p] = C2;
+            outT[(size_t)slot * 256 + p] = T;
+            outLast[(size_t)slot * 256 + p] = last;
+            // the walk stopped in this cell: every later cell is neutral here
+            if (live && T < thr) live = false;
+            M0 = fmaf(P, C0, M0);
+            M1 = fmaf(P, C1, M1);
+            M2 = fmaf(P, C2, M2);
+            P *= T;
         }
-        float* oc = outC + (size_t)slot * 768;
-        oc[p] = C0;
-        oc[256 + p] = C1;
-        oc[512 + p] = C2;
-        outT[(size_t)slot * 256 + p] = T;
-        outLast[(size_t)slot * 256 + p] = last;
-        // the walk stopped in this cell: every later cell is neutral here
-        if (live && T < thr) live = false;
-        M0 = fmaf(P, C0, M0);
-        M1 = fmaf(P, C1, M1);
-        M2 = fmaf(P, C2, M2);
-        P *= T;
-    }
-    if (image && px < V.W && py < V.H) {
-        const size_t HW = (size_t)V.W * V.H, pix = (size_t)py * V.W + px;
-        float* img = image + 3 * (size_t)V.pix_offset;
-        img[pix] = fmaf(P, V.bg[0], M0);
-        img[HW + pix] = fmaf(P, V.bg[1], M1);
-        img[2 * HW + pix] = fmaf(P, V.bg[2], M2);
-        T_final[V.pix_offset + pix] = P;
+        if (image && px < V.W && py < V.H) {
+            const size_t HW = (size_t)V.W * V.H, pix = (size_t)py * V.W + px;
+            float* img = image + 3 * (size_t)V.pix_offset;
+            img[pix] = fmaf(P, V.bg[0], M0);
+            img[HW + pix] = fmaf(P, V.bg[1], M1);
+            img[2 * HW + pix] = fmaf(P, V.bg[2], M2);
+            T_final[V.pix_offset + pix] = P;
+        }
     }
     if (STATS) {
         unsigned long long e = n_eval, c = n_con;
@@ -299,14 +552,16 @@ rgs_status render_fwd_launch(const rgs_projected* proj, const rgs_bins* bins, co
     // contribution from the stored T_k by division, which needs T_k to stay
     // a normal fp32 number (T_k >= 0.01 eps_T / P >= 2^-107)
     eps_T = fmaxf(eps_T, RGS_T_FLOOR);
+    const uint32_t heavy = (uint32_t)(total_tiles < (int64_t)RF_HEAVY ? total_tiles : (int64_t)RF_HEAVY);
+    const dim3 grid((unsigned)total_tiles + 3u * heavy);
     if (stats)
-        hipLaunchKernelGGL(k_render_fwd<true>, dim3((unsigned)total_tiles), dim3(256), 0, s, proj->rec, bins->vals,
-                           bins->slot_key, bins->slot_range, bins->tile_slot, bins->tile_order, vt, kd->box_lo, kd->box_hi,
+        hipLaunchKernelGGL(k_render_fwd<true>, grid, dim3(256), 0, s, proj->rec, bins->vals, bins->slot_key,
+                           bins->slot_range, bins->tile_slot, bins->tile_order, heavy, vt, kd->box_lo, kd->box_hi,
                            eps_T, out->C, out->T, out->last, reinterpret_cast<unsigned long long*>(stats), image,
                            T_final);
     else
-        hipLaunchKernelGGL(k_render_fwd<false>, dim3((unsigned)total_tiles), dim3(256), 0, s, proj->rec, bins->vals,
-                           bins->slot_key, bins->slot_range, bins->tile_slot, bins->tile_order, vt, kd->box_lo, kd->box_hi,
+        hipLaunchKernelGGL(k_render_fwd<false>, grid, dim3(256), 0, s, proj->rec, bins->vals, bins->slot_key,
+                           bins->slot_range, bins->tile_slot, bins->tile_order, heavy, vt, kd->box_lo, kd->box_hi,
                            eps_T, out->C, out->T, out->last, nullptr, image, T_final);
     return launch_check();
 }
@@ -336,11 +591,6 @@ __device__ __forceinline__ float swap16_sum(float x, float y) {
     asm volatile("" : "+v"(a), "+v"(b));  // keeps the two results apart (r[0] + r[1] otherwise folds to 2 r[0])
     return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
 }
-
-// Lane mask of a comparison (the compare writes it to scalar registers).
-__device__ __forceinline__ uint64_t wmask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-
-#define RGS_DPP(v, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (v)), (ctrl), 0xf, 0xf, false))
 
 __device__ __forceinline__ void wave_sum9(const float* g, int lane, float* out_v, float* out_8) {
     *out_8 = wave_sum_to_lane63(g[8]);

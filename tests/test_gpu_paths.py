@@ -125,3 +125,48 @@ def test_instance_lists_are_the_sorted_emission(n, W, H, L, mu, views, sync):
     assert nslot == len(start)
     assert np.array_equal(b["slot_range"][: 2 * nslot].cpu().numpy().reshape(-1, 2),
                           np.stack([start, np.append(start[1:], ninst)], 1))
+
+
+@pytest.mark.parametrize("n,W,H,L,mu,eps,stats,hot", [
+    (20000, 256, 256, 0, -3.4, 5e-5, False, False),   # one slot per tile, 256 tiles: all split
+    (20000, 250, 150, 3, -3.4, 5e-5, False, False),   # several slots, ragged edges
+    (6000, 250, 150, 2, -2.2, 1e-2, True, False),     # long lists that stop early; the counters
+    (6000, 130, 70, 2, -2.2, 0.0, False, False),      # never stop
+    (20000, 250, 150, 3, -3.4, 5e-5, False, True),    # colours that are not finite
+    (3, 16, 16, 1, -1.0, 5e-5, False, False),         # fewer instances than a wave's group of four
+])
+def test_split_tiles_equal_whole_tiles(n, W, H, L, mu, eps, stats, hot):
+    """The tiles of the longest lists are walked by four blocks of 4x4-pixel waves, the
+    others by one: a view alone (at most 256 tiles, all split) has the bits that it
+    has in a batch, where most tiles are whole."""
+    r = raster.Rasterizer()
+    p = scenes.scene_uniform(n, seed=n + W, D=1, mu_s=mu)
+    if hot:
+        p["sh"][:, ::100] = float("inf")
+    p = raster.to_device(p)
+    kd = r.kd_partition(p, L)
+    per_view = ((W + 15) // 16) * ((H + 15) // 16)
+    V = min(1024 // per_view + 2, 16)
+    cams = [scenes.orbit_camera(3.0, 0.3 + 0.5 * v, 0.3, W, H) for v in range(V)]
+    pairs = [torch.zeros(2, dtype=torch.int64, device="cuda") if stats else None for _ in range(2)]
+    batch = r.forward(p, kd, cams, eps, stats=pairs[0])
+    keep = [t.clone() for t in (batch.image, batch.T_final, batch.parts["C"], batch.parts["T"], batch.parts["last"])]
+    keys, nslot = batch.bins["slot_key"].clone(), int(batch.bins["counters"][2])
+    at = 0
+    for v, cam in enumerate(cams):
+        st = r.forward(p, kd, [cam], eps, stats=pairs[1])
+        m = int(st.bins["counters"][2])
+        assert torch.equal(keys[at: at + m].long() - v * per_view * (1 << L), st.bins["slot_key"][:m].long())
+        for kept, own, w, first in ((keep[0], st.image, 3 * W * H, 3 * v * W * H),
+                                    (keep[1], st.T_final, W * H, v * W * H),
+                                    (keep[2], st.parts["C"], 768 * m, 768 * at),
+                                    (keep[3], st.parts["T"], 256 * m, 256 * at),
+                                    (keep[4], st.parts["last"], 256 * m, 256 * at)):
+            a, b = kept.view(-1)[first: first + w], own.view(-1)[:w]
+            a, b = a.view(torch.int32), b.view(torch.int32)
+            nan = (a & 0x7FFFFFFF) > 0x7F800000  # any NaN for a NaN
+            assert torch.equal(nan, (b & 0x7FFFFFFF) > 0x7F800000)
+            assert torch.equal(a[~nan], b[~nan])
+        at += m
+    assert at == nslot
+    assert not stats or torch.equal(pairs[0], pairs[1])
