@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+from gpu_helpers import grad_close
 from paper_2406_11836_amd import raster, scenes, train
 
 pytestmark = pytest.mark.gpu
@@ -170,3 +172,30 @@ def test_split_tiles_equal_whole_tiles(n, W, H, L, mu, eps, stats, hot):
         at += m
     assert at == nslot
     assert not stats or torch.equal(pairs[0], pairs[1])
+
+
+@pytest.mark.parametrize("H,W", [
+    (1500, 1888),    # 16 full strips
+    (2003, 1405),    # a partial last strip and segment
+    (131, 20901),    # short segments: 118 columns, 32 rows and 3
+    (20901, 131),    # too narrow for strips: tiles
+])
+def test_large_view_loss(rast, H, W):
+    """The one-pass SSIM of large views: against the oracle, and a value that is not
+    finite changes the gradient within ten pixels of it only."""
+    rng = np.random.default_rng(H)
+    x = rng.uniform(size=(3, H, W)).astype(np.float32)
+    y = rng.uniform(size=(3, H, W)).astype(np.float32)
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    lv, d = rast.loss(xd, yd, 0.2)
+    ol, od = oracle.loss(x.astype(np.float64), y.astype(np.float64), 0.2)
+    assert abs(lv.item() - ol) <= 1e-5 * abs(ol)
+    ok, info = grad_close(d.cpu().numpy(), od, 1e-3, "dimage %dx%d" % (W, H))
+    assert ok, info
+    far = torch.ones_like(xd, dtype=torch.bool)
+    for c, py, px, v in ((0, 0, 0, float("nan")), (1, H // 2, W // 2, float("inf")), (2, H - 1, W - 1, float("nan"))):
+        xd[c, py, px] = v
+        far[c, max(py - 10, 0): py + 11, max(px - 10, 0): px + 11] = False
+    _, e = rast.loss(xd, yd, 0.2)
+    assert torch.equal(d[far], e[far])
+    assert not torch.isfinite(e[~far]).all()
