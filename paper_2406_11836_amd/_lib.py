@@ -144,12 +144,11 @@ def check(fn: str, status: int) -> int:
 def camera_struct(cam) -> Camera:
     c = Camera()
     R = [float(v) for v in list(getattr(cam["R"], "ravel", lambda: cam["R"])())]
-    for k in range(9):
-        c.R[k] = R[k]
-    for k in range(3):
-        c.t[k] = float(cam["t"][k])
-        c.campos[k] = float(cam["o"][k])
-        c.bg[k] = float(cam.get("bg", (0.0, 0.0, 0.0))[k])
+    t, o, bg = cam["t"], cam["o"], cam.get("bg", (0.0, 0.0, 0.0))
+    c.R[:] = R[:9]
+    c.t[:] = (float(t[0]), float(t[1]), float(t[2]))
+    c.campos[:] = (float(o[0]), float(o[1]), float(o[2]))
+    c.bg[:] = (float(bg[0]), float(bg[1]), float(bg[2]))
     c.fx, c.fy, c.cx, c.cy = float(cam["fx"]), float(cam["fy"]), float(cam["cx"]), float(cam["cy"])
     c.width, c.height, c.z_near = int(cam["W"]), int(cam["H"]), float(cam["z_near"])
     return c

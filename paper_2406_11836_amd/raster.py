@@ -25,12 +25,70 @@ from . import _lib as L
 PARAM_KEYS = ("means", "log_scales", "quats", "opacity", "sh")
 
 
+# Small and middle calls are bound by the host (the GPU waits 250 of 640 us of
+# a 20k training view), so their path makes few tensors and few ctypes objects:
+# pointers go as integers, the buffers of a pass are carved from one allocation
+# per stage, and a tensor for a part of it is made when it is asked for.
+ARENA_BYTES = 256 << 20  # above it, buffers are allocated one by one (large passes are not host-bound)
+_SIZE = {torch.uint8: 1, torch.int32: 4, torch.float32: 4, torch.int64: 8}
+
+
 def _p(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+class Carved(dict):
+    """Named tensors in one allocation; each is made when it is first asked for."""
+
+    def __init__(self, base, at):
+        super().__init__()
+        self._base, self._at = base, at
+
+    def ptr(self, key):
+        t = dict.get(self, key)
+        return self._base.data_ptr() + self._at[key][0] if t is None else t.data_ptr()
+
+    def __missing__(self, key):
+        off, n, dtype = self._at[key]
+        t = self._base[off: off + n * _SIZE[dtype]].view(dtype)
+        dict.__setitem__(self, key, t)
+        return t
+
+    def __setitem__(self, key, t):
+        self._at.setdefault(key, None)
+        dict.__setitem__(self, key, t)
+
+    def _full(self):
+        return {k: self[k] for k in self._at}
+
+    def get(self, key, default=None):
+        return self[key] if key in self._at else default
+
+    def keys(self):
+        return self._full().keys()
+
+    def values(self):
+        return self._full().values()
+
+    def items(self):
+        return self._full().items()
+
+    def __iter__(self):
+        return iter(self._full())
+
+    def __len__(self):
+        return len(self._at)
+
+    def __contains__(self, key):
+        return key in self._at
+
+
+def _ptr(d, key):
+    return d.ptr(key) if type(d) is Carved else d[key].data_ptr()
 
 
 def _mark(marks, name):
@@ -105,9 +163,8 @@ class FwdState:
 
     def proj_struct(self) -> L.Projected:
         s = L.Projected()
-        s.rec, s.bin = self.proj["rec"].data_ptr(), self.proj["bin"].data_ptr()
-        s.count = self.proj["count"].data_ptr()
-        s.depth = self.proj["depth"].data_ptr()
+        s.rec, s.bin = _ptr(self.proj, "rec"), _ptr(self.proj, "bin")
+        s.count, s.depth = _ptr(self.proj, "count"), _ptr(self.proj, "depth")
         return s
 
     def overflow(self) -> int:
@@ -117,7 +174,7 @@ class FwdState:
 
     def parts_struct(self) -> L.Partials:
         s = L.Partials()
-        s.C, s.T, s.last = self.parts["C"].data_ptr(), self.parts["T"].data_ptr(), self.parts["last"].data_ptr()
+        s.C, s.T, s.last = _ptr(self.parts, "C"), _ptr(self.parts, "T"), _ptr(self.parts, "last")
         return s
 
     def images(self):
@@ -157,6 +214,17 @@ class Rasterizer:
             t = torch.empty(int(nbytes * 1.25) + 256, dtype=torch.uint8, device=self.device)
             self._pool[key] = t
         return t[:nbytes].view(dtype)
+
+    def _carve(self, group, spec):
+        """Buffers (key, elements, dtype) of one stage by name."""
+        at, total = {}, 0
+        for key, n, dtype in spec:
+            n = int(max(n, 1))
+            at[key] = (total, n, dtype)
+            total += (n * _SIZE[dtype] + 255) & ~255
+        if total > ARENA_BYTES:
+            return {key: self._buf(key, n, dtype) for key, n, dtype in spec}
+        return Carved(self._buf(group, total, torch.uint8), at)
 
     # ------------------------------------------------------------ KD tree
     def kd_partition(self, params, Ldepth: int, d_factor: float = 3.0, own_mask: bool = True,
@@ -208,14 +276,10 @@ class Rasterizer:
         K = 1 << kd.L
         ranks = np.zeros((len(cams), K), np.int32)
         order = np.zeros(K, np.int32)
+        split, at, out = kd.split_host.ctypes.data, order.ctypes.data, ranks.ctypes.data
         for v, c in enumerate(cams):
             o = np.asarray(c["o"], np.float32)
-            rk = np.zeros(K, np.int32)
-            L.check("rgs_cell_order", self.lib.rgs_cell_order(kd.L, kd.split_host.ctypes.data_as(C.c_void_p),
-                                                               o.ctypes.data_as(C.c_void_p),
-                                                               order.ctypes.data_as(C.c_void_p),
-                                                               rk.ctypes.data_as(C.c_void_p)))
-            ranks[v] = rk
+            L.check("rgs_cell_order", self.lib.rgs_cell_order(kd.L, split, o.ctypes.data, at, out + 4 * K * v))
         return ranks
 
     # ------------------------------------------------------------ forward
@@ -246,44 +310,38 @@ class Rasterizer:
         # packed on the host into pinned memory and copied on the stream without waiting
         # (torch's pinned allocator does not reuse the block before the copy is done)
         host = torch.empty(vb, dtype=torch.uint8, pin_memory=True)
-        L.check("rgs_views_pack", lib.rgs_views_pack(cam_arr, V, kd.L, ranks.ctypes.data_as(C.c_void_p),
-                                                     None if vis is None else vis.ctypes.data_as(C.c_void_p),
-                                                     C.c_void_p(host.data_ptr())))
+        L.check("rgs_views_pack", lib.rgs_views_pack(cam_arr, V, kd.L, ranks.ctypes.data,
+                                                     None if vis is None else vis.ctypes.data, host.data_ptr()))
         views.copy_(host, non_blocking=True)
         _mark(marks, "views")
         g = gaussians_struct(params)
         ks = kd.struct()
         m = V * n
-        proj = dict(rec=self._buf("rec", m * L.REC_FLOATS, torch.float32), bin=self._buf("bin", m * 8, torch.int32),
-                    count=self._buf("count", m, torch.int32),
-                    depth=self._buf("depth", m, torch.float32))
-        ps = L.Projected(proj["rec"].data_ptr(), proj["bin"].data_ptr(), proj["count"].data_ptr(),
-                         proj["depth"].data_ptr())
+        proj = self._carve("proj", (("rec", m * L.REC_FLOATS, torch.float32), ("bin", m * 8, torch.int32),
+                                    ("count", m, torch.int32), ("depth", m, torch.float32)))
+        ps = L.Projected(_ptr(proj, "rec"), _ptr(proj, "bin"), _ptr(proj, "count"), _ptr(proj, "depth"))
         L.check("rgs_project_sh", lib.rgs_project_sh(C.byref(g), cam_arr, V, _p(views), C.byref(ks), int(cells), C.byref(ps),
                                                      stream))
         _mark(marks, "project")
         T = int(lib.rgs_total_tiles(cam_arr, V))
         K = 1 << kd.L
-        bins = dict(pair_src=self._buf("pair_src", m, torch.int32), pair_off=self._buf("pair_off", m + 1, torch.int32),
-                    pair_rank=self._buf("pair_rank", m, torch.int32), tile_slot=self._buf("tile_slot", T + 1, torch.int32),
-                    tile_order=self._buf("tile_order", T, torch.int32),
-                    counters=self._buf("counters", 4, torch.int32))
         cap = max(self.capacity_hint, 1)
         # no host wait in binning when an earlier pass sized the buffers and the
         # slot bound stays small (the caller checks FwdState.overflow())
         use_async = no_sync and self.capacity_hint > 0 and min(cap, T * K) <= (1 << 18)
         while True:
             slot_cap = min(cap, T * K)
-            bins["keys"] = self._buf("keys", cap, torch.int32)
-            bins["vals"] = self._buf("vals", cap, torch.int64)
-            bins["slot_key"] = self._buf("slot_key", slot_cap, torch.int32)
-            bins["slot_range"] = self._buf("slot_range", 2 * slot_cap, torch.int32)
-            bins["slot_order"] = self._buf("slot_order", slot_cap, torch.int32)
+            bins = self._carve("bins", (("pair_src", m, torch.int32), ("pair_off", m + 1, torch.int32),
+                                        ("pair_rank", m, torch.int32), ("tile_slot", T + 1, torch.int32),
+                                        ("tile_order", T, torch.int32), ("counters", 4, torch.int32),
+                                        ("keys", cap, torch.int32), ("vals", cap, torch.int64),
+                                        ("slot_key", slot_cap, torch.int32), ("slot_range", 2 * slot_cap, torch.int32),
+                                        ("slot_order", slot_cap, torch.int32)))
             bs = L.Bins()
             bs.capacity, bs.slot_capacity = cap, slot_cap
             for k in ("keys", "vals", "pair_src", "pair_off", "pair_rank", "slot_key", "slot_range", "tile_slot",
                       "slot_order", "tile_order", "counters"):
-                setattr(bs, k, bins[k].data_ptr())
+                setattr(bs, k, _ptr(bins, k))
             ws_bytes = lib.rgs_bin_sort_workspace(n, V, T, kd.L, cap)
             ws = self._buf("bin_ws", ws_bytes, torch.uint8)
             need = C.c_int64(0)
@@ -307,9 +365,9 @@ class Rasterizer:
             # actual slot count instead (one small device-to-host read)
             slot_cap = max(int(bins["counters"][2].item()), 1)
             bs.slot_capacity = slot_cap
-        parts = dict(C=self._buf("C", slot_cap * 768, torch.float32), T=self._buf("T", slot_cap * 256, torch.float32),
-                     last=self._buf("last", slot_cap * 256, torch.int32))
-        pt = L.Partials(parts["C"].data_ptr(), parts["T"].data_ptr(), parts["last"].data_ptr())
+        parts = self._carve("parts", (("C", slot_cap * 768, torch.float32), ("T", slot_cap * 256, torch.float32),
+                                      ("last", slot_cap * 256, torch.int32)))
+        pt = L.Partials(_ptr(parts, "C"), _ptr(parts, "T"), _ptr(parts, "last"))
         npix = sum(int(c["W"]) * int(c["H"]) for c in cams)
         image = self._buf("image", 3 * npix, torch.float32)
         T_final = self._buf("T_final", npix, torch.float32)

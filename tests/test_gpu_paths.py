@@ -199,3 +199,32 @@ def test_large_view_loss(rast, H, W):
     _, e = rast.loss(xd, yd, 0.2)
     assert torch.equal(d[far], e[far])
     assert not torch.isfinite(e[~far]).all()
+
+
+@pytest.mark.parametrize("reuse", [False, True])
+def test_one_allocation_per_stage_equals_separate_buffers(monkeypatch, reuse):
+    """Buffers carved from one allocation, and one by one (large passes): the same
+    pass, the same names, and a replaced buffer is the one the backward reads."""
+    p = raster.to_device(scenes.scene_uniform(3000, seed=5, D=1, mu_s=-3.0))
+    cams = [scenes.orbit_camera(3.0, 0.3 + v, 0.3, 150, 90) for v in range(2)]
+    d = torch.randn(3 * 2 * 150 * 90, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    got = []
+    for limit in (raster.ARENA_BYTES, 0):
+        monkeypatch.setattr(raster, "ARENA_BYTES", limit)
+        r = raster.Rasterizer(reuse=reuse)
+        kd = r.kd_partition(p, 2)
+        for _ in range(2):  # the second pass knows its capacity
+            st = r.forward(p, kd, cams, 5e-5)
+        assert type(st.parts) is (raster.Carved if limit else dict)
+        m = int(st.bins["counters"][2])
+        g = r.backward(st, p, d)
+        got.append([st.image, st.T_final, st.parts["C"][: 768 * m], st.bins["slot_key"][:m]] +
+                   [g[k] for k in raster.PARAM_KEYS])
+        names = [{k: (v.numel(), v.dtype) for k, v in x.items()} for x in (st.proj, st.bins, st.parts)]
+        got[-1].append(names)
+        assert all(len(x) == len(y) and all(k in x for k in y) and list(x) == list(y)
+                   for x, y in zip((st.proj, st.bins, st.parts), names))
+        st.parts["T"] = torch.zeros_like(st.parts["T"])
+        assert st.parts_struct().T == st.parts["T"].data_ptr()
+    for a, b in zip(*got):
+        assert torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b
