@@ -228,3 +228,46 @@ def test_one_allocation_per_stage_equals_separate_buffers(monkeypatch, reuse):
         assert st.parts_struct().T == st.parts["T"].data_ptr()
     for a, b in zip(*got):
         assert torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b
+
+
+@pytest.mark.parametrize("n,Ld,kind", [
+    (1, 1, "normal"), (2, 6, "normal"), (85, 2, "normal"), (700, 3, "normal"),   # no room for the list; empty nodes
+    (5000, 4, "equal"),          # every member matches every prefix
+    (9000, 6, "grid"),           # few distinct values, both zeros
+    (300000, 5, "narrow"),       # blocks with more 16-bit matches than the list takes
+    (300000, 6, "normal"),       # the list; 64 cells, two mask words
+    (70000, 3, "odd"),           # centres and scales that are not finite
+])
+@pytest.mark.parametrize("rule", [0, 1])
+def test_partition_at_its_edges(rast, n, Ld, kind, rule):
+    """Splits, leaves, counts, ownership and bounds against the oracle, bit for bit."""
+    rng = np.random.default_rng(n + Ld)
+    p = scenes.scene_uniform(n, seed=n, D=0, mu_s=-3.0)
+    m = rng.normal(size=(3, n)).astype(np.float32) * 50
+    if kind == "equal":
+        m[:] = 1.25
+    elif kind == "grid":
+        m = np.round(m / 20) * 20 * np.where(rng.uniform(size=m.shape) < 0.5, 1, -1)
+    elif kind == "narrow":
+        m = 1000 + rng.uniform(size=m.shape) * 3
+    p["means"] = np.ascontiguousarray(m, np.float32)
+    if kind == "odd":
+        p["means"][0, :40], p["means"][1, 40:80] = np.inf, -np.inf
+        p["log_scales"][1, 100:200] = 200.0
+        p["log_scales"][2, 150:300] = -np.inf
+    kd = rast.kd_partition(raster.to_device(p), Ld, rule=rule)
+    o = oracle.kd_partition(p["means"], p["log_scales"], Ld, 3.0, rule=rule)
+    K = 1 << Ld
+    assert np.array_equal(kd.split.cpu().numpy()[: K - 1].view(np.uint32), o["split"].view(np.uint32))
+    assert np.array_equal(kd.center_cell.cpu().numpy(), o["center_cell"])
+    assert np.array_equal(kd.counts.cpu().numpy(), o["counts"])
+    own = kd.own_mask.cpu().numpy().view(np.uint32).reshape(o["own_mask"].shape)
+    assert np.array_equal(own, o["own_mask"])
+    b = kd.cell_bounds_host
+    smax = np.exp(p["log_scales"].astype(np.float64)).astype(np.float32).max(0)
+    for k in range(K):
+        sel = o["center_cell"] == k
+        lo, hi, sc = ((p["means"][:, sel].min(1), p["means"][:, sel].max(1), smax[sel].max()) if sel.any()
+                      else (np.inf, -np.inf, 0.0))
+        assert np.array_equal(b[0:3, k], np.broadcast_to(lo, 3)) and np.array_equal(b[3:6, k], np.broadcast_to(hi, 3))
+        assert b[6, k] == sc
