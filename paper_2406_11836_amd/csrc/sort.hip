@@ -75,18 +75,45 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_reduce(const uint32_t* __
 
 // Exclusive scan, in place, of the sums of the first ceil(dn / tile) tiles;
 // the total to *total if non-null.
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_partials(uint32_t* __restrict__ partial, DevN dn, int64_t tile,
-                                                                uint32_t* __restrict__ total) {
-    __shared__ uint32_t s_wave[4];
+// (One block: 16384 sums per round, loaded together; 100M entries have 24K sums
+// of 4096, which took 32 us in rounds of 256.)
+static constexpr int SP_THREADS = 1024, SP_ITEMS = 16;
+__global__ __launch_bounds__(SP_THREADS) void k_scan_partials(uint32_t* __restrict__ partial, DevN dn, int64_t tile,
+                                                              uint32_t* __restrict__ total) {
+    __shared__ uint32_t s_w[SP_THREADS / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t m = (dn.get() + tile - 1) / tile;
     uint32_t carry = 0;
-    for (int64_t b = 0; b < m; b += SCAN_THREADS) {
-        int64_t i = b + threadIdx.x;
-        uint32_t v = i < m ? partial[i] : 0u;
-        uint32_t ex;
-        uint32_t tot = block_excl_scan_256(v, s_wave, &ex);
-        if (i < m) partial[i] = carry + ex;
-        carry += tot;
+    for (int64_t b = 0; b < m; b += SP_THREADS * SP_ITEMS) {
+        const int64_t i = b + (int64_t)threadIdx.x * SP_ITEMS;
+        uint32_t v[SP_ITEMS], acc = 0;
+        if (i + SP_ITEMS <= m) {
+#pragma unroll
+            for (int k = 0; k < SP_ITEMS; k += 4) {
+                const uint4 q = *reinterpret_cast<const uint4*>(partial + i + k);
+                v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < SP_ITEMS; ++k) v[k] = i + k < m ? partial[i + k] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < SP_ITEMS; ++k) acc += v[k];
+        const uint32_t inc = wave_incl_scan(acc);
+        if (lane == 63) s_w[w] = inc;
+        __syncthreads();
+        uint32_t run = carry + inc - acc;
+#pragma unroll
+        for (int k = 0; k < SP_THREADS / 64; ++k) {
+            run += k < w ? s_w[k] : 0u;
+            carry += s_w[k];
+        }
+#pragma unroll
+        for (int k = 0; k < SP_ITEMS; ++k) {
+            if (i + k < m) partial[i + k] = run;
+            run += v[k];
+        }
+        __syncthreads();
     }
     if (threadIdx.x == 0 && total) *total = carry;
 }
@@ -216,7 +243,7 @@ rgs_status scan_tile_reduce(const uint32_t* in, int64_t n, int marks, uint32_t* 
 }
 
 rgs_status scan_tile_sums(uint32_t* partial, DevN dn, int64_t tile, uint32_t* total, hipStream_t s) {
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(SCAN_THREADS), 0, s, partial, dn, tile, total);
+    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(SP_THREADS), 0, s, partial, dn, tile, total);
     return launch_check();
 }
 
@@ -233,7 +260,7 @@ rgs_status exclusive_scan_u32_dev(const uint32_t* in, uint32_t* out, DevN dn, in
     const unsigned grid = (unsigned)(tiles < 1 ? 1 : (dn.p && tiles > DEV_GRID ? DEV_GRID : tiles));
     if (n_max > 0 && !sums_ready)
         hipLaunchKernelGGL(k_scan_reduce, dim3(grid), dim3(SCAN_THREADS), 0, s, in, dn, marks, partial);
-    if (!fold) hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(SCAN_THREADS), 0, s, partial, dn, (int64_t)SCAN_TILE, total);
+    if (!fold) hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(SP_THREADS), 0, s, partial, dn, (int64_t)SCAN_TILE, total);
     hipLaunchKernelGGL(k_scan_apply, dim3(grid), dim3(SCAN_THREADS), 0, s, in, dn, marks, partial, fold ? 1 : 0,
                        total, tl, out);
     if (!fold && tl.cnt) {

@@ -271,3 +271,19 @@ def test_partition_at_its_edges(rast, n, Ld, kind, rule):
                       else (np.inf, -np.inf, 0.0))
         assert np.array_equal(b[0:3, k], np.broadcast_to(lo, 3)) and np.array_equal(b[3:6, k], np.broadcast_to(hi, 3))
         assert b[6, k] == sc
+
+
+@pytest.mark.parametrize("n", [1, 63, 4095, 4096, 4097, 70001])
+def test_kept_pairs_in_index_order(rast, n):
+    """The compaction's bit words at tile and word edges: the pairs of a pass are the
+    kept Gaussians, by depth, ties in index order."""
+    p = scenes.scene_uniform(n, seed=n, D=0, mu_s=-4.0)
+    p["means"][2] = np.round(p["means"][2] * 4) / 4  # many equal depths
+    cam = scenes.orbit_camera(3.0, 0.3, 0.0, 96, 64)
+    p = raster.to_device(p)
+    st = rast.forward(p, rast.kd_partition(p, 1), [cam], 5e-5)
+    count, depth = st.proj["count"][:n].cpu().numpy(), st.proj["depth"][:n].cpu().numpy()
+    kept = np.nonzero(count)[0]
+    m = int(st.bins["counters"][0])
+    assert m == len(kept)
+    assert np.array_equal(st.bins["pair_src"][:m].cpu().numpy(), kept[np.argsort(depth[kept], kind="stable")])
