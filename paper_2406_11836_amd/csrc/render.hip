@@ -1101,9 +1101,9 @@ static BwdWs carve_bwd(const rgs_bins* bins, void* ws) {
 // over the slot's pixels: it walks instances 0 .. w - 1), so that the
 // heaviest blocks start first; a slot with w = 0 (no contribution) is not
 // launched.  Two passes without global atomics (which serialise on a handful
-// of class counters): k_slot_work, SW_SLOTS slots per block, a wave per slot
+// of class counters): k_slot_work, SW_SLOTS slots (times `rounds`) per block, a wave per slot
 // at a time (256 `last` values, four per lane), stores w and the block's
-// class counts as one row of a table; k_slot_place, the same SW_SLOTS slots
+// class counts as one row of a table; k_slot_place, the same slots
 // per block, derives every class's start and the block's offset in it from
 // the table and places its slots (the order inside a class is the launch
 // order only and affects no result).
@@ -1138,7 +1138,7 @@ __global__ __launch_bounds__(256) void k_slot_work(const uint32_t* __restrict__ 
                                                    const uint32_t* __restrict__ counters, uint32_t* __restrict__ work,
                                                    uint32_t* __restrict__ wtab, uint32_t* __restrict__ touched,
                                                    int64_t touched_words, const uint32_t* __restrict__ pair_off,
-                                                   uint32_t* __restrict__ first_pair) {
+                                                   uint32_t* __restrict__ first_pair, int rounds) {
     __shared__ uint32_t s_c[SW_CLS];
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < touched_words; i += (int64_t)gridDim.x * 256)
         touched[i] = 0u;
@@ -1147,8 +1147,8 @@ __global__ __launch_bounds__(256) void k_slot_work(const uint32_t* __restrict__ 
     if (threadIdx.x < SW_CLS) s_c[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t ns = (int64_t)counters[2];
-    const int64_t base = (int64_t)blockIdx.x * SW_SLOTS + wv * (SW_SLOTS / 4);
-    for (int k0 = 0; k0 < SW_SLOTS / 4; k0 += SW_CHUNK) {
+    const int64_t base = ((int64_t)blockIdx.x * SW_SLOTS + wv * (SW_SLOTS / 4)) * rounds;
+    for (int k0 = 0; k0 < SW_SLOTS / 4 * rounds; k0 += SW_CHUNK) {
         // all loads first (a slot past the count reads slot 0 and is not stored;
         // this launch has at least one slot of capacity)
         uint4 v[SW_CHUNK];
@@ -1175,12 +1175,13 @@ __global__ __launch_bounds__(256) void k_slot_work(const uint32_t* __restrict__ 
 __global__ __launch_bounds__(256) void k_slot_place(const uint32_t* __restrict__ work,
                                                     const uint32_t* __restrict__ counters,
                                                     const uint32_t* __restrict__ wtab, uint32_t* __restrict__ n_launch,
-                                                    uint32_t* __restrict__ order) {
+                                                    uint32_t* __restrict__ order, int rounds) {
     constexpr int NG = 256 / SW_CLS;  // row groups per class column
     __shared__ uint32_t s_tot[NG][SW_CLS], s_bef[NG][SW_CLS], s_base[SW_CLS], s_c[SW_CLS];
     const int t = threadIdx.x, c = t % SW_CLS, g = t / SW_CLS;
     const int64_t ns = (int64_t)counters[2];
-    const int nblk = (int)((ns + SW_SLOTS - 1) / SW_SLOTS);
+    const int64_t per = (int64_t)SW_SLOTS * rounds;
+    const int nblk = (int)((ns + per - 1) / per);
     {  // the table's column c, rows g, g + NG, ...: all blocks, and the blocks before this one
         uint32_t tot = 0, bef = 0;
         for (int r0 = g; r0 < nblk; r0 += 8 * NG) {
@@ -1220,11 +1221,13 @@ __global__ __launch_bounds__(256) void k_slot_place(const uint32_t* __restrict__
         if (blockIdx.x == 0) *n_launch = run;
     }
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * SW_SLOTS + t;
-    const uint32_t wk = (t < SW_SLOTS && i < ns) ? work[i] : 0u;
-    if (wk) {
-        const int k = slot_class(wk);
-        order[s_base[k] + atomicAdd(&s_c[k], 1u)] = (uint32_t)i;
+    for (int64_t o = t; o < per; o += 256) {
+        const int64_t i = (int64_t)blockIdx.x * per + o;
+        const uint32_t wk = i < ns ? work[i] : 0u;
+        if (wk) {
+            const int k = slot_class(wk);
+            order[s_base[k] + atomicAdd(&s_c[k], 1u)] = (uint32_t)i;
+        }
     }
 }
 
@@ -1246,10 +1249,14 @@ rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_
                            bins->pair_off, bins->counters, w.first_pair);
         return launch_check();
     }
-    const unsigned nblk = (unsigned)((slot_bound + SW_SLOTS - 1) / SW_SLOTS);
+    // every block of the placement reads the whole class table: many slots take
+    // more per block, still hundreds of blocks (16 views, 825k slots: placement
+    // 1551 us with 64 slots per block, now 124)
+    const int rounds = slot_bound >= (1 << 20) ? 16 : (slot_bound >= (1 << 16) ? 4 : 1);
+    const unsigned nblk = (unsigned)((slot_bound + SW_SLOTS * rounds - 1) / (SW_SLOTS * rounds));
     hipLaunchKernelGGL(k_slot_work, dim3(nblk), dim3(256), 0, s, parts->last, bins->counters, w.work, w.wtab, w.touched,
-                       (int64_t)w.touched_words, bins->pair_off, w.first_pair);
-    hipLaunchKernelGGL(k_slot_place, dim3(nblk), dim3(256), 0, s, w.work, bins->counters, w.wtab, w.wcls, w.order);
+                       (int64_t)w.touched_words, bins->pair_off, w.first_pair, rounds);
+    hipLaunchKernelGGL(k_slot_place, dim3(nblk), dim3(256), 0, s, w.work, bins->counters, w.wtab, w.wcls, w.order, rounds);
     if (stats)
         hipLaunchKernelGGL(k_render_bwd<true>, dim3((unsigned)slot_bound), dim3(128), 0, s, proj->rec, bins->vals,
                            bins->slot_key, bins->slot_range, w.order, w.wcls, vt, kd->box_lo, kd->box_hi,

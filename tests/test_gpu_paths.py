@@ -287,3 +287,24 @@ def test_kept_pairs_in_index_order(rast, n):
     m = int(st.bins["counters"][0])
     assert m == len(kept)
     assert np.array_equal(st.bins["pair_src"][:m].cpu().numpy(), kept[np.argsort(depth[kept], kind="stable")])
+
+
+def test_many_slots_launch_order(rast):
+    """From 65536 slots on the launch order's tables take more slots per block: the
+    first view has the gradients it has alone (the other views' image gradients are
+    zero; a later view's instances lie elsewhere in the waves of the pair sums)."""
+    W, H, L = 640, 480, 6
+    p = raster.to_device(scenes.scene_uniform(40000, seed=3, D=1, mu_s=-3.0))
+    kd = rast.kd_partition(p, L)
+    cams = [scenes.orbit_camera(3.0, 0.3 + 0.4 * v, 0.3, W, H) for v in range(16)]
+    d = torch.randn(3 * W * H, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    r = raster.Rasterizer()
+    a = r.forward(p, kd, cams[:1], 5e-5)
+    ga = r.backward(a, p, d)
+    b = r.forward(p, kd, cams, 5e-5)
+    assert int(a.bins["counters"][2]) < 65536 <= int(b.bins["counters"][2])
+    z = torch.zeros(16, 3 * W * H, device="cuda")
+    z[0] = d
+    gb = r.backward(b, p, z.view(-1))
+    for k in raster.PARAM_KEYS:
+        assert torch.equal(ga[k], gb[k]) and torch.count_nonzero(ga[k]) > 0, k
