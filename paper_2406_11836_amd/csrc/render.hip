@@ -30,6 +30,9 @@ namespace rgs {
 
 static constexpr int RD_BATCH = 64;
 static constexpr int RD_REC = 9;   // floats per backward record (36 bytes, read back contiguously)
+// A pair's flag: no record (0), its entry is the sum of its records, or (pairs whose
+// instances span several waves) the range of waves whose partials make it up.
+static constexpr uint8_t PS_SUM = 1, PS_SPAN = 2;
 static constexpr int PS_REC = 12;  // floats per per-pair / per-wave sum (48 bytes, float4-aligned)
 // The backward's launch order: slots per block of its two passes, and the
 // size classes (half octaves of the instances a slot is walked over)
@@ -659,6 +662,7 @@ __global__ __launch_bounds__(128) void k_render_bwd(const float* __restrict__ re
                                                     const uint32_t* __restrict__ partLast, const float* __restrict__ dC,
                                                     const float* __restrict__ dT, float* __restrict__ records,
                                                     uint32_t* __restrict__ touched,
+                                                    const uint32_t* __restrict__ counters, uint32_t* __restrict__ flags,
                                                     unsigned long long* __restrict__ stats) {
     constexpr int NB = 64;
     __shared__ float4 sA[NB], sB[NB], sCl[NB];
@@ -667,6 +671,9 @@ __global__ __launch_bounds__(128) void k_render_bwd(const float* __restrict__ re
     __shared__ float sG[2][NB][9];
     __shared__ uint32_t s_max[2];
     __shared__ uint64_t s_wrote[2];  // per wave: the batch's instances it wrote half sums for
+    // the pairs' flags for the pair reduction (a byte each, where the slots' work was)
+    for (uint64_t i = (uint64_t)blockIdx.x * 128u + threadIdx.x; i < ((uint64_t)counters[0] + 3u) / 4u; i += (uint64_t)gridDim.x * 128u)
+        flags[i] = 0u;
     if (blockIdx.x >= *n_launch) return;
     const uint32_t slot = slot_order[blockIdx.x];
     const int L = vt->L, K = 1 << L;
@@ -869,12 +876,16 @@ __global__ __launch_bounds__(128) void k_render_bwd(const float* __restrict__ re
 //     load of the next 64 pair offsets; a segmented inclusive scan (fixed tree of
 //     shuffles) sums each pair's records within the wave.  The wave's first
 //     segment (pair begun before it) and last segment (pair going on after
-//     it) are kept as wave partials; every pair gets its psum[rank] entry in
-//     the wave where it ends: its sum if it lies in that wave, else the
-//     first and last wave it spans (a flag in the entry's last word).
-//  2. k_pair_gather: thread per (view, Gaussian): zero if culled, else the
-//     pair's psum entry, or, for a pair spanning several waves, its tail
-//     partial + whole-wave partials + head partial, in instance order.
+//     it) are kept as wave partials; a pair with a record gets its psum[rank]
+//     entry and a flag: its sum if it lies in one wave, else the first and
+//     last wave it spans.  Most waves of a large batch have no record (16
+//     views: 73 %) and end at once.
+//  2. k_pair_gather: thread per (view, Gaussian): zero if culled or without a
+//     flag, else the pair's psum entry, or, for a pair spanning several waves,
+//     its tail partial + whole-wave partials + head partial, in instance order.
+// us, reduction + gather: 16 views, 767M instances, 5 % with a record, 55M pairs
+// 4714 + 1899 -> 2286 + 1148; 1M at 1600x1060 56 + 32 -> 45 + 24; 16M at
+// 3840x2160 78 + 179 -> 41 + 190 (when every pair's entry was written and read).
 // first_pair[w] = the pair holding instance 64 w: each pair writes the waves
 // that start inside it (one thread per pair, grid-stride over the device count).
 __device__ __forceinline__ void wave_first_pairs(const uint32_t* __restrict__ pair_off,
@@ -898,25 +909,26 @@ __global__ __launch_bounds__(256) void k_pair_seg(const float* __restrict__ reco
                                                   const uint32_t* __restrict__ pair_off,
                                                   const uint32_t* __restrict__ counters,
                                                   const uint32_t* __restrict__ first_pair, float* __restrict__ psum,
-                                                  float* __restrict__ wpart) {
+                                                  float* __restrict__ wpart, uint8_t* __restrict__ flags) {
     const int lane = threadIdx.x & 63;
     const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const uint32_t n_pairs = counters[0], n_inst = counters[1];
     const int64_t j0 = w * 64;
     if (j0 >= (int64_t)n_inst) return;  // uniform per wave
+    const uint2 tw = reinterpret_cast<const uint2*>(touched)[w];
+    const uint64_t has_mask = (uint64_t)tw.y << 32 | tw.x;
+    if (has_mask == 0ull) return;  // no record: its pairs' entries stay empty, its partials unread
     const int64_t j = j0 + lane;
     const bool valid = j < (int64_t)n_inst;
     // the records first (they do not depend on the pair lookup); an instance
     // without a record (behind its tile's last contributors) counts as zero
     float v[9];
-    bool has;
+    const bool has = (has_mask >> lane) & 1ull;
     {
-        const uint32_t jc = (uint32_t)(valid ? j : (int64_t)n_inst - 1);
-        has = valid && ((touched[jc >> 5] >> (jc & 31u)) & 1u);
 #pragma unroll
         for (int c = 0; c < 9; ++c) v[c] = 0.f;
         if (has) {
-            const float* rp = records + (size_t)jc * RD_REC;
+            const float* rp = records + (size_t)j * RD_REC;
 #pragma unroll
             for (int c = 0; c < 9; ++c) v[c] = rp[c];
         }
@@ -959,14 +971,12 @@ __global__ __launch_bounds__(256) void k_pair_seg(const float* __restrict__ reco
             if (tk) v[c] += u;                                                                                     \
         }                                                                                                          \
     }
-    if (__ballot(has) != 0ull) {  // a wave without records sums zeros: no scan
-        RGS_SEG_STEP(0x111, 0xf, lane - 1 >= seg0)             // row_shr:1
-        RGS_SEG_STEP(0x112, 0xf, lane - 2 >= seg0)             // row_shr:2
-        RGS_SEG_STEP(0x114, 0xf, lane - 4 >= seg0)             // row_shr:4
-        RGS_SEG_STEP(0x118, 0xf, lane - 8 >= seg0)             // row_shr:8
-        RGS_SEG_STEP(0x142, 0xa, (row & 1) && seg0 < 16 * row)  // row_bcast:15
-        RGS_SEG_STEP(0x143, 0xc, row >= 2 && seg0 < 32)         // row_bcast:31
-    }
+    RGS_SEG_STEP(0x111, 0xf, lane - 1 >= seg0)             // row_shr:1
+    RGS_SEG_STEP(0x112, 0xf, lane - 2 >= seg0)             // row_shr:2
+    RGS_SEG_STEP(0x114, 0xf, lane - 4 >= seg0)             // row_shr:4
+    RGS_SEG_STEP(0x118, 0xf, lane - 8 >= seg0)             // row_shr:8
+    RGS_SEG_STEP(0x142, 0xa, (row & 1) && seg0 < 16 * row)  // row_bcast:15
+    RGS_SEG_STEP(0x143, 0xc, row >= 2 && seg0 < 32)         // row_bcast:31
 #undef RGS_SEG_STEP
     const int pos_next = __shfl_down(pos, 1, 64);
     const bool next_valid = lane < 63 && j + 1 < (int64_t)n_inst;
@@ -978,13 +988,16 @@ __global__ __launch_bounds__(256) void k_pair_seg(const float* __restrict__ reco
     const bool goes_on = e_at > j0 + 64;
     const float4 o0 = make_float4(v[0], v[1], v[2], v[3]), o1 = make_float4(v[4], v[5], v[6], v[7]),
                  o2 = make_float4(v[8], 0.f, 0.f, 0.f);
-    if (!goes_on) {
+    if (has_mask & le_mask & ~((1ull << seg0) - 1ull)) {  // the segment has a record
         float4* q = reinterpret_cast<float4*>(psum + (size_t)r * PS_REC);
-        if (!began_before) {
+        if (!goes_on && !began_before) {
             q[0] = o0; q[1] = o1; q[2] = o2;
-        } else {  // spans waves pb / 64 .. (e_at - 1) / 64: its sum is in the wave partials
-            q[2] = make_float4(0.f, __uint_as_float((uint32_t)(pb >> 6)), __uint_as_float((uint32_t)((e_at - 1) >> 6)),
-                               __uint_as_float(1u));
+            flags[r] = PS_SUM;
+        } else {
+            // spans waves pb / 64 .. (e_at - 1) / 64: its sum is in the wave partials
+            // (every wave with one of its records writes the same)
+            q[2] = make_float4(0.f, __uint_as_float((uint32_t)(pb >> 6)), __uint_as_float((uint32_t)((e_at - 1) >> 6)), 0.f);
+            flags[r] = PS_SPAN;
         }
     }
     if (began_before) {
@@ -1006,6 +1019,8 @@ __device__ __forceinline__ void acc_rec(const float* __restrict__ p, float4& a0,
 }
 
 __global__ __launch_bounds__(256) void k_pair_gather(const float* __restrict__ psum, const float* __restrict__ wpart,
+                                                     const uint32_t* __restrict__ touched,
+                                                     const uint8_t* __restrict__ flags,
                                                      const uint32_t* __restrict__ count,
                                                      const int32_t* __restrict__ pair_rank,
                                                      const uint32_t* __restrict__ counters, int64_t m,
@@ -1017,19 +1032,22 @@ __global__ __launch_bounds__(256) void k_pair_gather(const float* __restrict__ p
     const int32_t r = count[sidx] > 0u ? pair_rank[sidx] : -1;
     if (r >= 0 && (uint32_t)r < counters[0]) {  // a pass that ran out of capacity has no pairs
         const float4* q = reinterpret_cast<const float4*>(psum + (size_t)r * PS_REC);
-        const float4 x = q[0], y = q[1], z = q[2];
-        if (__float_as_uint(z.w) == 0u) {  // the pair lies in one wave: its sum
-            a0 = x;
-            a1 = y;
-            a8 = z.x;
-        } else {
-            const uint32_t wb = __float_as_uint(z.y), we = __float_as_uint(z.z);
+        const uint8_t flag = flags[r];
+        if (flag == PS_SUM) {
+            a0 = q[0];
+            a1 = q[1];
+            a8 = q[2].x;
+        } else if (flag == PS_SPAN) {
+            const uint32_t wb = __float_as_uint(q[2].y), we = __float_as_uint(q[2].z);
             // the range the pair reduction wrote lies in the instance array (checked all the same)
             const uint32_t nw = (uint32_t)(((uint64_t)counters[1] + 63u) >> 6);
             if (wb < we && we < nw) {
-                acc_rec(wpart + ((size_t)wb * 2 + 1) * PS_REC, a0, a1, a8);  // tail of the first wave
-                for (uint32_t w = wb + 1; w < we; ++w) acc_rec(wpart + (size_t)w * 2 * PS_REC, a0, a1, a8);  // whole waves
-                acc_rec(wpart + (size_t)we * 2 * PS_REC, a0, a1, a8);       // head of the last wave
+                // tail of the first wave, whole waves, head of the last one; a wave
+                // without records wrote no partials
+                for (uint32_t w = wb; w <= we; ++w) {
+                    const uint2 tw = reinterpret_cast<const uint2*>(touched)[w];
+                    if ((tw.x | tw.y) != 0u) acc_rec(wpart + ((size_t)w * 2 + (w == wb ? 1 : 0)) * PS_REC, a0, a1, a8);
+                }
             }
         }
     }
@@ -1087,7 +1105,7 @@ static BwdWs carve_bwd(const rgs_bins* bins, void* ws) {
                                                ((nw * 2 * PS_REC * sizeof(float) + 255) & ~size_t(255)));
     w.touched = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.first_pair) +
                                             ((nw * sizeof(uint32_t) + 255) & ~size_t(255)));
-    w.touched_words = (c + 31) / 32;
+    w.touched_words = 2 * ((c + 63) / 64);  // (whole 64-instance waves)
     w.wcls = w.touched + w.touched_words;
     const size_t tw = ((c + 31) / 32 + 64) * sizeof(uint32_t);
     w.work = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.touched) + ((tw + 255) & ~size_t(255)));
@@ -1244,6 +1262,7 @@ rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_
         const int64_t nb = ((int64_t)w.touched_words + 255) / 256;
         hipLaunchKernelGGL(k_clear_words, dim3((unsigned)(nb < 1024 ? (nb > 0 ? nb : 1) : 1024)), dim3(256), 0, s,
                            w.touched, (int64_t)w.touched_words);
+        hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(256), 0, s, w.work, bins->capacity);  // (the pairs' flags)
         const int64_t pb = (bins->capacity + 255) / 256;
         hipLaunchKernelGGL(k_wave_first, dim3((unsigned)(pb < 2048 ? (pb > 0 ? pb : 1) : 2048)), dim3(256), 0, s,
                            bins->pair_off, bins->counters, w.first_pair);
@@ -1261,11 +1280,12 @@ rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_
         hipLaunchKernelGGL(k_render_bwd<true>, dim3((unsigned)slot_bound), dim3(128), 0, s, proj->rec, bins->vals,
                            bins->slot_key, bins->slot_range, w.order, w.wcls, vt, kd->box_lo, kd->box_hi,
                            parts->T, parts->last, dparts->dC, dparts->dT, w.records, w.touched,
-                           reinterpret_cast<unsigned long long*>(stats));
+                           bins->counters, w.work, reinterpret_cast<unsigned long long*>(stats));
     else
         hipLaunchKernelGGL(k_render_bwd<false>, dim3((unsigned)slot_bound), dim3(128), 0, s, proj->rec, bins->vals,
                            bins->slot_key, bins->slot_range, w.order, w.wcls, vt, kd->box_lo, kd->box_hi,
-                           parts->T, parts->last, dparts->dC, dparts->dT, w.records, w.touched, nullptr);
+                           parts->T, parts->last, dparts->dC, dparts->dT, w.records, w.touched,
+                           bins->counters, w.work, nullptr);
     return launch_check();
 }
 
@@ -1279,12 +1299,13 @@ rgs_status pair_reduce_launch(const rgs_bins* bins, const rgs_projected* proj, i
     // (the records call wrote first_pair)
     if (bins->capacity > 0) {
         hipLaunchKernelGGL(k_pair_seg, dim3((unsigned)((bins->capacity + 255) / 256)), dim3(256), 0, s, w.records,
-                           w.touched, bins->pair_off, bins->counters, w.first_pair, w.psum, w.wpart);
+                           w.touched, bins->pair_off, bins->counters, w.first_pair, w.psum, w.wpart,
+                           reinterpret_cast<uint8_t*>(w.work));
     }
     RGS_LAUNCH_CHECK();
     if (m > 0)
         hipLaunchKernelGGL(k_pair_gather, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, w.psum, w.wpart,
-                           proj->count, bins->pair_rank, bins->counters, m, dproj);
+                           w.touched, reinterpret_cast<const uint8_t*>(w.work), proj->count, bins->pair_rank, bins->counters, m, dproj);
     return launch_check();
 }
 

@@ -308,3 +308,39 @@ def test_many_slots_launch_order(rast):
     gb = r.backward(b, p, z.view(-1))
     for k in raster.PARAM_KEYS:
         assert torch.equal(ga[k], gb[k]) and torch.count_nonzero(ga[k]) > 0, k
+
+
+@pytest.mark.parametrize("n,mu,W,H", [(50, 0.0, 640, 480), (3000, -2.0, 333, 201), (40000, -3.5, 333, 201), (1, -1.0, 40, 24)])
+def test_pair_sums_of_the_records(monkeypatch, n, mu, W, H):
+    """Pairs inside a wave, spanning waves, and waves without a record: the sums of the
+    backward's records, against a float64 sum of those in the workspace."""
+    r = raster.Rasterizer()
+    p = raster.to_device(scenes.scene_uniform(n, seed=n, D=0, mu_s=mu))
+    st = r.forward(p, r.kd_partition(p, 3), [scenes.orbit_camera(3.0, 0.3, 0.3, W, H)], 1e-2)
+    spaces = []
+    empty = raster.Rasterizer._empty
+
+    def kept(self, size, dtype):
+        t = empty(self, size, dtype)
+        if dtype == torch.uint8:
+            spaces.append(t)
+        return t
+    monkeypatch.setattr(raster.Rasterizer, "_empty", kept)
+    g = r.backward(st, p, torch.randn(3 * W * H, device="cuda", generator=torch.Generator("cuda").manual_seed(2)))
+    ws, cap = spaces[-1], st.bins_struct.capacity
+    up = lambda x: (x + 255) & ~255
+    nw = (cap + 63) // 64
+    at = up(cap * 36) + up(cap * 48) + up(nw * 96) + up(nw * 4)
+    npair, ninst = (int(x) for x in st.bins["counters"][:2].cpu())
+    words = ws[at: at + 8 * ((ninst + 63) // 64)].cpu().numpy()
+    has = np.unpackbits(words, bitorder="little")[:ninst].astype(bool)
+    rec = ws[: 36 * ninst].view(torch.float32).view(ninst, 9).cpu().numpy().astype(np.float64)
+    rec[~has] = 0.0
+    off = st.bins["pair_off"][: npair + 1].cpu().numpy().view(np.uint32).astype(np.int64)
+    src = st.bins["pair_src"][:npair].cpu().numpy()
+    want, mag = np.zeros((n, 9)), np.zeros((n, 9))
+    for q in range(npair):
+        want[src[q]] = rec[off[q]: off[q + 1]].sum(0)
+        mag[src[q]] = np.abs(rec[off[q]: off[q + 1]]).sum(0) * (64 + (off[q + 1] - off[q]) // 64)
+    got = g["_dproj"][: 9 * n].view(9, n).cpu().numpy().T.astype(np.float64)
+    assert has.any() and np.all(np.abs(got - want) <= 2.0 ** -24 * mag)
