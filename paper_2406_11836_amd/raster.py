@@ -331,6 +331,7 @@ class Rasterizer:
         use_async = no_sync and self.capacity_hint > 0 and min(cap, T * K) <= (1 << 18)
         while True:
             slot_cap = min(cap, T * K)
+            bins = ws = None  # (of a first, too small attempt)
             bins = self._carve("bins", (("pair_src", m, torch.int32), ("pair_off", m + 1, torch.int32),
                                         ("pair_rank", m, torch.int32), ("tile_slot", T + 1, torch.int32),
                                         ("tile_order", T, torch.int32), ("counters", 4, torch.int32),
