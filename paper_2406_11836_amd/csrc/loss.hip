@@ -531,13 +531,13 @@ __global__ __launch_bounds__(SC, 3) void k_ssim(const float* __restrict__ x, con
 
 // One marching pass from SSIM_MARCH values on, where the strips fit the width
 // (at most a quarter of them beyond it): us for the loss, tiles / marching:
-// 1920x1080 89 / 88, 2000x1200 110 / 94, 2560x1440 162 / 128, 3840x2160 367 / 236,
+// 1600x1060 76 / 79, 1920x1080 91 / 86, 2000x1200 112 / 92, 2560x1440 162 / 128, 3840x2160 367 / 236,
 // 5000x3000 644 / 415; a quarter of the strips' time on the chip is start-up at
 // smaller views (997x663: 36 / 54), and 130 columns take two strips (125 / 138 at
 // 20000 rows).  Segments are as long as one round of blocks
 // allows (3 waves per SIMD: 6 blocks per CU), since each computes ten rows
 // above and below its own: 2048 blocks, two rounds, take 302 us at 3840x2160.
-static constexpr int64_t SSIM_MARCH = 8000000;
+static constexpr int64_t SSIM_MARCH = 6000000;
 static constexpr int SSIM_BLOCKS = 1536, SSIM_ROWS = 32;
 
 size_t loss_ws_bytes(int H, int W) {
