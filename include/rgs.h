@@ -427,6 +427,12 @@ rgs_status rgs_merge_partials_bwd(const float *d_image, const float *d_T_final, 
  * d mx, d my, d ca, d cb, d cc, d alpha, d r, d g, d b (zero for culled
  * pairs; cb is the off-diagonal conic entry). */
 size_t rgs_render_bwd_workspace(int64_t capacity);
+/* The same for bins of slot_capacity slots and at most `pairs` pairs
+ * (n_views * n), never more than for the capacity alone: a large batch has
+ * far fewer pairs and slots than instances (16 views of 4M Gaussians, 882M
+ * instances: 33.9 instead of 80.3 GiB).  The backward takes a workspace of
+ * either size. */
+size_t rgs_render_bwd_workspace_for(int64_t capacity, int64_t slot_capacity, int64_t pairs);
 rgs_status rgs_render_partial_bwd(const rgs_partials_grad *dparts, const rgs_partials *parts,
                                   const rgs_bins *bins, const rgs_projected *proj, int64_t n,
                                   const rgs_camera *cams, int32_t n_views, const void *views_dev,

@@ -37,12 +37,12 @@ rgs_status bin_sort(const rgs_projected* proj, int64_t n, int n_views, const Vie
 rgs_status render_fwd_launch(const rgs_projected* proj, const rgs_bins* bins, const ViewTable* vt, const rgs_kdtree* kd,
                              float eps_T, const rgs_partials* out, uint64_t* stats, int64_t total_tiles, hipStream_t s,
                              float* image = nullptr, float* T_final = nullptr);
-size_t render_bwd_ws_bytes(int64_t capacity);
+size_t render_bwd_ws_bytes(int64_t capacity, int64_t slots, int64_t pairs);
 rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_partials* parts, const rgs_bins* bins,
-                                     const rgs_projected* proj, const ViewTable* vt, const rgs_kdtree* kd, void* ws,
-                                     uint64_t* stats, int64_t slot_bound, hipStream_t s);
+                                     const rgs_projected* proj, int64_t pairs, const ViewTable* vt, const rgs_kdtree* kd,
+                                     void* ws, size_t ws_bytes, uint64_t* stats, int64_t slot_bound, hipStream_t s);
 rgs_status pair_reduce_launch(const rgs_bins* bins, const rgs_projected* proj, int64_t n, int n_views, float* dproj,
-                              void* ws, hipStream_t s);
+                              void* ws, size_t ws_bytes, hipStream_t s);
 rgs_status merge_fwd_launch(const rgs_partials* parts, const rgs_bins* bins, const ViewTable* vt, int64_t total_tiles,
                             float* image, float* T_final, hipStream_t s);
 rgs_status merge_bwd_launch(const float* dimage, const float* dTfinal, const rgs_partials* parts, const rgs_bins* bins,
@@ -561,7 +561,12 @@ rgs_status rgs_merge_partials_bwd(const float* d_image, const float* d_T_final, 
 
 size_t rgs_render_bwd_workspace(int64_t capacity) {
     if (capacity < 0) return 0;
-    return render_bwd_ws_bytes(capacity);
+    return render_bwd_ws_bytes(capacity, capacity, capacity);
+}
+
+size_t rgs_render_bwd_workspace_for(int64_t capacity, int64_t slot_capacity, int64_t pairs) {
+    if (capacity < 0 || slot_capacity < 0 || pairs < 0) return 0;
+    return render_bwd_ws_bytes(capacity, slot_capacity, pairs);
 }
 
 static bool bwd_args_ok(const rgs_partials_grad* dparts, const rgs_partials* parts, const rgs_bins* bins,
@@ -571,8 +576,8 @@ static bool bwd_args_ok(const rgs_partials_grad* dparts, const rgs_partials* par
     if (!dparts || !dparts->dC || !dparts->dT || !parts || !parts->T || !parts->last || !bins_ok(bins) || !proj_ok(proj) ||
         n < 0 || !cams_ok(cams, n_views) || !views_dev || !kd || !kd->box_lo || !kd->box_hi)
         return false;
-    if (!ws_ok(ws, ws_bytes, render_bwd_ws_bytes(bins->capacity))) return false;
     const size_t m = (size_t)n_views * (size_t)n;
+    if (!ws_ok(ws, ws_bytes, render_bwd_ws_bytes(bins->capacity, bins->slot_capacity, (int64_t)m))) return false;
     const size_t sc = (size_t)(bins->slot_capacity > 0 ? bins->slot_capacity : 0);
     const int K = 1 << kd->L;
     const Spans ins =
@@ -589,18 +594,18 @@ rgs_status rgs_render_partial_bwd_records(const rgs_partials_grad* dparts, const
                                           rgs_stream stream) {
     if (!bwd_args_ok(dparts, parts, bins, proj, n, cams, n_views, views_dev, kd, ws, ws_bytes, {{stats, 16}}))
         return RGS_E_ARG;
-    return render_bwd_records_launch(dparts, parts, bins, proj, reinterpret_cast<const ViewTable*>(views_dev), kd, ws,
-                                     stats, slot_bound_of(bins, cams, n_views, kd->L), S(stream));
+    return render_bwd_records_launch(dparts, parts, bins, proj, n_views * n, reinterpret_cast<const ViewTable*>(views_dev),
+                                     kd, ws, ws_bytes, stats, slot_bound_of(bins, cams, n_views, kd->L), S(stream));
 }
 
 rgs_status rgs_pair_reduce(const rgs_bins* bins, const rgs_projected* proj, int64_t n, int32_t n_views, float* d_proj,
                            void* ws, size_t ws_bytes, rgs_stream stream) {
     if (!bins_ok(bins) || !proj_ok(proj) || n < 0 || n_views < 1 || n_views > RGS_MAX_VIEWS || !d_proj) return RGS_E_ARG;
-    if (!ws_ok(ws, ws_bytes, render_bwd_ws_bytes(bins->capacity))) return RGS_E_ARG;
     const size_t m = (size_t)n_views * (size_t)n;
+    if (!ws_ok(ws, ws_bytes, render_bwd_ws_bytes(bins->capacity, bins->slot_capacity, (int64_t)m))) return RGS_E_ARG;
     if (!disjoint({{d_proj, 36 * m}}, concat(concat(proj_spans(proj, m), bins_spans(bins, m, 0)), {{ws, ws_bytes}})))
         return RGS_E_ARG;
-    return pair_reduce_launch(bins, proj, n, n_views, d_proj, ws, S(stream));
+    return pair_reduce_launch(bins, proj, n, n_views, d_proj, ws, ws_bytes, S(stream));
 }
 
 rgs_status rgs_render_partial_bwd(const rgs_partials_grad* dparts, const rgs_partials* parts, const rgs_bins* bins,
@@ -611,10 +616,11 @@ rgs_status rgs_render_partial_bwd(const rgs_partials_grad* dparts, const rgs_par
         !bwd_args_ok(dparts, parts, bins, proj, n, cams, n_views, views_dev, kd, ws, ws_bytes,
                      {{d_proj, (size_t)36 * (size_t)n_views * (size_t)n}}))
         return RGS_E_ARG;
-    rgs_status st = render_bwd_records_launch(dparts, parts, bins, proj, reinterpret_cast<const ViewTable*>(views_dev),
-                                              kd, ws, nullptr, slot_bound_of(bins, cams, n_views, kd->L), S(stream));
+    rgs_status st = render_bwd_records_launch(dparts, parts, bins, proj, n_views * n,
+                                              reinterpret_cast<const ViewTable*>(views_dev), kd, ws, ws_bytes, nullptr,
+                                              slot_bound_of(bins, cams, n_views, kd->L), S(stream));
     if (st != RGS_OK) return st;
-    return pair_reduce_launch(bins, proj, n, n_views, d_proj, ws, S(stream));
+    return pair_reduce_launch(bins, proj, n, n_views, d_proj, ws, ws_bytes, S(stream));
 }
 
 rgs_status rgs_project_sh_bwd(const float* d_proj, const rgs_gaussians* g, const rgs_projected* proj,

@@ -1062,20 +1062,36 @@ __global__ __launch_bounds__(256) void k_pair_gather(const float* __restrict__ p
     dproj[8 * m + sidx] = a8;
 }
 
-// Backward workspace: 36-byte records and 48-byte per-pair sums (pairs <=
-// instances <= capacity), two 48-byte partials and the first pair per 64
-// instances.
-size_t render_bwd_ws_bytes(int64_t capacity) {
-    const size_t c = (size_t)(capacity > 0 ? capacity : 1);
-    const size_t rec = c * RD_REC * sizeof(float), ps = c * PS_REC * sizeof(float);
-    const size_t nw = (c + 63) / 64;
-    const size_t wp = nw * 2 * PS_REC * sizeof(float);
-    const size_t tw = ((c + 31) / 32 + 64) * sizeof(uint32_t);  // bitmask + launch count
-    const size_t tab = (c + SW_SLOTS - 1) / SW_SLOTS * SW_CLS * sizeof(uint32_t);  // launch-order class counts
-    return ((rec + 255) & ~size_t(255)) + ((ps + 255) & ~size_t(255)) + ((wp + 255) & ~size_t(255)) +
-           ((nw * sizeof(uint32_t) + 255) & ~size_t(255)) + ((tw + 255) & ~size_t(255)) +
-           2 * ((c * sizeof(uint32_t) + 255) & ~size_t(255)) + ((tab + 255) & ~size_t(255)) + 256;
+// Backward workspace for an instance capacity, at most `slots` slots and at most
+// `pairs` pairs (neither can exceed the instances): 36-byte records; 48-byte
+// per-pair sums; two 48-byte partials and the first pair per 64 instances; a bit
+// per instance; a word per slot twice, of which the first array is the pairs'
+// flag bytes later, and the launch order's class counts.  Sized by the capacity
+// alone everything but the records comes to 62 bytes per instance, of which
+// nothing like that is used where instances are many per pair and slot (16 views,
+// 882M instances, 64M pairs, 0.8M slots: 80.3 GiB, against 33.9 GiB so).
+static size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
+
+struct BwdSizes {
+    size_t c, slots, pairs;
+    size_t rec() const { return up256(c * RD_REC * sizeof(float)); }
+    size_t psum() const { return up256(pairs * PS_REC * sizeof(float)); }
+    size_t wpart() const { return up256((c + 63) / 64 * 2 * PS_REC * sizeof(float)); }
+    size_t first() const { return up256((c + 63) / 64 * sizeof(uint32_t)); }
+    size_t touched() const { return up256(((c + 31) / 32 + 64) * sizeof(uint32_t)); }  // bitmask + launch count
+    size_t work() const { return up256((slots > (pairs + 3) / 4 ? slots : (pairs + 3) / 4) * sizeof(uint32_t)); }
+    size_t order() const { return up256(slots * sizeof(uint32_t)); }
+    size_t tab() const { return up256((slots + SW_SLOTS - 1) / SW_SLOTS * SW_CLS * sizeof(uint32_t)); }
+    size_t all() const { return rec() + psum() + wpart() + first() + touched() + work() + order() + tab() + 256; }
+};
+
+static BwdSizes bwd_sizes(int64_t capacity, int64_t slots, int64_t pairs) {
+    const int64_t c = capacity > 0 ? capacity : 1;
+    auto most = [c](int64_t x) { return (size_t)(x < 1 ? 1 : (x < c ? x : c)); };
+    return BwdSizes{(size_t)c, most(slots), most(pairs)};
 }
+
+size_t render_bwd_ws_bytes(int64_t capacity, int64_t slots, int64_t pairs) { return bwd_sizes(capacity, slots, pairs).all(); }
 
 struct BwdWs {
     float *records, *psum, *wpart;
@@ -1083,34 +1099,35 @@ struct BwdWs {
     uint32_t* touched;  // bit j: instance j (emission position) has a record
     size_t touched_words;
     uint32_t* wcls;     // the number of slots launched (after the bitmask)
-    uint32_t* work;     // per slot: instances the backward visits (its largest `last`)
+    uint32_t* work;     // per slot: instances the backward visits (its largest `last`); then the pairs' flags
+    int64_t flag_words;
     uint32_t* order;    // the backward's launch order
-    uint32_t* wtab;     // [blocks of SW_SLOTS slots][32] class counts
+    uint32_t* wtab;     // [blocks of SW_SLOTS slots][SW_CLS] class counts
 };
 
 __global__ __launch_bounds__(256) void k_clear_words(uint32_t* __restrict__ p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0u;
 }
 
-static BwdWs carve_bwd(const rgs_bins* bins, void* ws) {
-    const size_t c = (size_t)(bins->capacity > 0 ? bins->capacity : 1);
-    const size_t rec_bytes = (c * RD_REC * sizeof(float) + 255) & ~size_t(255);
-    const size_t ps_bytes = (c * PS_REC * sizeof(float) + 255) & ~size_t(255);
+// A workspace of the size for the capacity alone is laid out by it, a smaller one
+// by the slots and pairs; the records and the reduction see the same bytes.
+static BwdWs carve_bwd(const rgs_bins* bins, int64_t pairs, void* ws, size_t ws_bytes) {
+    const int64_t cap = bins->capacity;
+    BwdSizes z = bwd_sizes(cap, cap, cap);
+    if (ws_bytes < z.all()) z = bwd_sizes(cap, bins->slot_capacity, pairs);
     BwdWs w;
-    w.records = reinterpret_cast<float*>(ws);
-    w.psum = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + rec_bytes);
-    w.wpart = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + rec_bytes + ps_bytes);
-    const size_t nw = (c + 63) / 64;
-    w.first_pair = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.wpart) +
-                                               ((nw * 2 * PS_REC * sizeof(float) + 255) & ~size_t(255)));
-    w.touched = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.first_pair) +
-                                            ((nw * sizeof(uint32_t) + 255) & ~size_t(255)));
-    w.touched_words = 2 * ((c + 63) / 64);  // (whole 64-instance waves)
+    char* p = reinterpret_cast<char*>(ws);
+    w.records = reinterpret_cast<float*>(p);
+    w.psum = reinterpret_cast<float*>(p += z.rec());
+    w.wpart = reinterpret_cast<float*>(p += z.psum());
+    w.first_pair = reinterpret_cast<uint32_t*>(p += z.wpart());
+    w.touched = reinterpret_cast<uint32_t*>(p += z.first());
+    w.touched_words = 2 * ((z.c + 63) / 64);  // (whole 64-instance waves)
     w.wcls = w.touched + w.touched_words;
-    const size_t tw = ((c + 31) / 32 + 64) * sizeof(uint32_t);
-    w.work = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.touched) + ((tw + 255) & ~size_t(255)));
-    w.order = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.work) + ((c * sizeof(uint32_t) + 255) & ~size_t(255)));
-    w.wtab = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(w.order) + ((c * sizeof(uint32_t) + 255) & ~size_t(255)));
+    w.work = reinterpret_cast<uint32_t*>(p += z.touched());
+    w.flag_words = (int64_t)((z.pairs + 3) / 4);
+    w.order = reinterpret_cast<uint32_t*>(p += z.work());
+    w.wtab = reinterpret_cast<uint32_t*>(p += z.order());
     return w;
 }
 
@@ -1251,9 +1268,9 @@ __global__ __launch_bounds__(256) void k_slot_place(const uint32_t* __restrict__
 
 // The partial-render backward alone: per-instance records into the workspace.
 rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_partials* parts, const rgs_bins* bins,
-                                     const rgs_projected* proj, const ViewTable* vt, const rgs_kdtree* kd, void* ws,
-                                     uint64_t* stats, int64_t slot_bound, hipStream_t s) {
-    const BwdWs w = carve_bwd(bins, ws);
+                                     const rgs_projected* proj, int64_t pairs, const ViewTable* vt, const rgs_kdtree* kd,
+                                     void* ws, size_t ws_bytes, uint64_t* stats, int64_t slot_bound, hipStream_t s) {
+    const BwdWs w = carve_bwd(bins, pairs, ws, ws_bytes);
     // no record yet: the bitmask is cleared by a fill kernel (not a memset:
     // the call may be captured), with the launch order's first pass
     // (and the pair reduction's first pair of every 64 instances, which it
@@ -1262,7 +1279,7 @@ rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_
         const int64_t nb = ((int64_t)w.touched_words + 255) / 256;
         hipLaunchKernelGGL(k_clear_words, dim3((unsigned)(nb < 1024 ? (nb > 0 ? nb : 1) : 1024)), dim3(256), 0, s,
                            w.touched, (int64_t)w.touched_words);
-        hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(256), 0, s, w.work, bins->capacity);  // (the pairs' flags)
+        hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(256), 0, s, w.work, w.flag_words);  // (the pairs' flags)
         const int64_t pb = (bins->capacity + 255) / 256;
         hipLaunchKernelGGL(k_wave_first, dim3((unsigned)(pb < 2048 ? (pb > 0 ? pb : 1) : 2048)), dim3(256), 0, s,
                            bins->pair_off, bins->counters, w.first_pair);
@@ -1291,9 +1308,9 @@ rgs_status render_bwd_records_launch(const rgs_partials_grad* dparts, const rgs_
 
 // The per-pair sums of the records in the workspace.
 rgs_status pair_reduce_launch(const rgs_bins* bins, const rgs_projected* proj, int64_t n, int n_views, float* dproj,
-                              void* ws, hipStream_t s) {
-    const BwdWs w = carve_bwd(bins, ws);
+                              void* ws, size_t ws_bytes, hipStream_t s) {
     const int64_t m = (int64_t)n_views * n;
+    const BwdWs w = carve_bwd(bins, m, ws, ws_bytes);
     // one wave per 64 instances up to the capacity; waves past the device-side
     // instance count return at once
     // (the records call wrote first_pair)

@@ -358,8 +358,10 @@ class Rasterizer:
                 continue
             L.check("rgs_bin_sort", st)
             break
+        # the sort's workspace is not read again (12 bytes per instance and 20 per pair: 11 GiB
+        # of a 16-view batch that the backward's buffers need)
+        ws = None
         _mark(marks, "bin_sort")
-        n_inst = int(bs.n_instances)
         slot_cap = int(bs.slot_capacity)
         if slot_cap > (1 << 18) and not use_async:
             # large bound (many views / tiles): size the partial maps by the
@@ -387,7 +389,7 @@ class Rasterizer:
             _mark(marks, "merge")
         return FwdState(n=n, cams=list(cams), cam_arr=cam_arr, kd=kd, views=views, proj=proj, bins=bins,
                         bins_struct=bs, parts=parts, image=image, T_final=T_final, eps_T=eps_T, total_tiles=T,
-                        slot_capacity=slot_cap, keep=[ws, n_inst])
+                        slot_capacity=slot_cap)
 
     # ------------------------------------------------------------ backward
     def backward(self, st: FwdState, params, d_image: torch.Tensor, d_T_final: torch.Tensor | None = None,
@@ -412,7 +414,11 @@ class Rasterizer:
         ks = st.kd.struct()
         m = V * st.n
         dproj = self._empty(9 * m, torch.float32)
+        # a small pass asks for what the capacity alone gives, the same block pass after pass;
+        # a large one for what its slots and pairs can use (less than half in a batch of views)
         ws_bytes = lib.rgs_render_bwd_workspace(bs.capacity)
+        if ws_bytes > ARENA_BYTES:
+            ws_bytes = lib.rgs_render_bwd_workspace_for(bs.capacity, bs.slot_capacity, m)
         ws = self._empty(ws_bytes, torch.uint8)
         L.check("rgs_render_partial_bwd_records",
                 lib.rgs_render_partial_bwd_records(C.byref(pgs), C.byref(pt), C.byref(bs), C.byref(ps), st.n, st.cam_arr,

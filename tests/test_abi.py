@@ -243,3 +243,19 @@ def test_aliased_buffers_are_rejected(lib):
     # binning: the sorted keys over the projected records
     assert lib.rgs_bin_sort(C.byref(ps), 1000, cam, 1, C.c_void_p(0x6000000), 0, C.byref(bs), None,
                             C.c_void_p(0x20000000 + 256), 1 << 30, None) == E
+
+
+def test_bwd_workspace_by_slots_and_pairs(lib):
+    """The backward's workspace for known slots and pairs: what the records and the
+    sums of 64 instances take, 48 bytes per pair, 9 per slot and its share of the
+    class table; at most the size for the capacity alone, which it is when neither bound helps."""
+    f, full = lib.rgs_render_bwd_workspace_for, lib.rgs_render_bwd_workspace
+    for c in (0, 1, 63, 64, 65, 12345, 882_000_000):
+        for s in (0, 1, 100, 1 << 40):
+            for p in (0, 1, 100, 1 << 40):
+                assert 36 * c <= f(c, s, p) <= full(c)
+        assert f(c, 1 << 40, 1 << 40) == full(c)
+    # 16 views of 4M Gaussians
+    c, s, p = 882_000_000, 825_000, 64_000_000
+    assert f(c, s, p) <= 36 * c + (96 + 4 + 8) * (c // 64 + 1) + 49 * p + 12 * s + 8192 < 35 << 30
+    assert f(-1, 1, 1) == f(1, -1, 1) == f(1, 1, -1) == 0
