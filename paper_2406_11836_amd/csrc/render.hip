@@ -228,22 +228,21 @@ __global__ __launch_bounds__(256, 8) void k_render_fwd(const float* __restrict__
             sA[NB] = sCl[NB] = make_float4(0.f, 0.f, 0.f, 0.f);
             sB[NB] = make_float4(0.f, 0.f, -1.f, 0.f);
         }
-        // the stream of the tile's instances (its slots are contiguous in the list):
         // the source of the next batch's record is loaded ahead
-        uint32_t src = 0, tile_end = 0;
+        uint32_t src = 0;
         const uint32_t* vhi = reinterpret_cast<const uint32_t*>(vals) + 1;  // high words: the sources
-        auto next_src = [&](uint32_t at) {  // (past the tile's end: its last instance)
+        auto next_src = [&](uint32_t at, uint32_t lim) {  // of the slot that ends at lim (past it: its last instance)
             const uint32_t i = at + (uint32_t)tid;
-            src = vhi[2 * (size_t)(i < tile_end ? i : tile_end - 1u)];
+            src = vhi[2 * (size_t)(i < lim ? i : max(lim, 1u) - 1u)];
         };
-        if (s0 < s1) {
-            tile_end = slot_range[2 * (s1 - 1) + 1];
-            next_src(slot_range[2 * s0]);
-        }
+        if (s0 < s1) next_src(slot_range[2 * s0], slot_range[2 * s0 + 1]);
         int par = 0;  // parity of the batch (its flags are read while the next one's are written)
         for (uint32_t slot = s0; slot < s1; ++slot) {
             const uint32_t key = slot_key[slot];
             const uint32_t begin = slot_range[2 * slot], end = slot_range[2 * slot + 1];
+            // the tile's next slot, which need not follow in the list (a caller's table of some cells)
+            const uint32_t sn = slot + 1 < s1 ? slot + 1 : slot;
+            const uint32_t sn_begin = slot_range[2 * sn], sn_end = slot_range[2 * sn + 1];
             const int cell = V.cell_of_rank[key & ((1u << L) - 1u)];
             const float blo0 = box_lo[cell], blo1 = box_lo[K + cell], blo2 = box_lo[2 * K + cell];
             const float bhi0 = box_hi[cell], bhi1 = box_hi[K + cell], bhi2 = box_hi[2 * K + cell];
@@ -274,7 +273,8 @@ __global__ __launch_bounds__(256, 8) void k_render_fwd(const float* __restrict__
                 // colours are >= 0: all finite if their sum is
                 const uint64_t odd_m = wmask(tid < nb && !((rc.x + rc.y) + rc.z < INFINITY));
                 if (lane == 0) s_flag[par][w] = (am != 0ull ? 1u : 0u) | (odd_m != 0ull ? 2u : 0u);
-                next_src(next);
+                if (next < end) next_src(next, end);
+                else next_src(sn_begin, sn_end);
                 __syncthreads();
                 const uint32_t fl = s_flag[par][0] | s_flag[par][1] | s_flag[par][2] | s_flag[par][3];
                 par ^= 1;

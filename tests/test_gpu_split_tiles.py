@@ -1,0 +1,53 @@
+"""The longest tiles' four-block walk against the others' walk, where they could part."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_11836_amd import _lib, raster, scenes
+
+pytestmark = pytest.mark.gpu
+SPLIT = 256  # tiles of a launch that are split
+
+
+@pytest.fixture(scope="module")
+def rast():
+    return raster.Rasterizer()
+
+
+def test_a_slot_table_of_some_cells(rast):
+    """A caller that renders some of the cells passes a table of their slots, whose
+    instances do not follow each other: the same partials as in the whole table
+    (without early termination no cell depends on another)."""
+    W, H, L = 250, 150, 3
+    p = raster.to_device(scenes.scene_uniform(4000, seed=12, D=1, mu_s=-3.4))
+    kd = rast.kd_partition(p, L)
+    cam = scenes.orbit_camera(3.0, 0.3, 0.3, W, H)
+    st = rast.forward(p, kd, [cam], 0.0)
+    S = int(st.bins["counters"][2])
+    key = st.bins["slot_key"][:S].cpu().numpy()
+    tiles = st.total_tiles
+    assert tiles <= SPLIT and st.T_final.min().item() > 2.0 ** -90
+    sel = np.nonzero(np.isin(key & ((1 << L) - 1), (0, 2, 5, 7)))[0]
+    assert (np.bincount(key[sel] >> L) > 1).sum() > 50
+    idx = torch.from_numpy(sel).cuda()
+    bs = st.bins_struct
+    sk = torch.zeros(st.slot_capacity, dtype=torch.int32, device="cuda")
+    sr = torch.zeros(2 * st.slot_capacity, dtype=torch.int32, device="cuda")
+    sk[: sel.size] = st.bins["slot_key"][idx]
+    sr[: 2 * sel.size] = st.bins["slot_range"][: 2 * S].view(S, 2)[idx].reshape(-1)
+    ts = torch.from_numpy(np.searchsorted(key[sel] >> L, np.arange(tiles + 1)).astype(np.int32)).cuda()
+    own = {k: torch.zeros_like(st.parts[k]) for k in ("C", "T", "last")}
+    pt = _lib.Partials(*[own[k].data_ptr() for k in ("C", "T", "last")])
+    saved = (bs.slot_key, bs.slot_range, bs.tile_slot)
+    bs.slot_key, bs.slot_range, bs.tile_slot = sk.data_ptr(), sr.data_ptr(), ts.data_ptr()
+    try:
+        ps, ks = st.proj_struct(), kd.struct()
+        _lib.check("rgs_render_partial", rast.lib.rgs_render_partial(
+            C.byref(ps), st.n, C.byref(bs), st.cam_arr, 1, st.views.data_ptr(), C.byref(ks), 0.0, C.byref(pt), None,
+            torch.cuda.current_stream().cuda_stream))
+    finally:
+        bs.slot_key, bs.slot_range, bs.tile_slot = saved
+    for k, w in (("C", 768), ("T", 256), ("last", 256)):
+        assert torch.equal(own[k][: w * sel.size].view(-1, w), st.parts[k][: w * S].view(S, w)[idx]), k
