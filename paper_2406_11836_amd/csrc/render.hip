@@ -246,8 +246,10 @@ __global__ __launch_bounds__(256, 8) void k_render_fwd(const float* __restrict__
             const int cell = V.cell_of_rank[key & ((1u << L) - 1u)];
             const float blo0 = box_lo[cell], blo1 = box_lo[K + cell], blo2 = box_lo[2 * K + cell];
             const float bhi0 = box_hi[cell], bhi1 = box_hi[K + cell], bhi2 = box_hi[2 * K + cell];
-            // a pixel that has stopped (or is off the image) takes no contribution
-            const float thr = live ? eps_T / P : INFINITY;
+            // a pixel that has stopped (or is off the image) takes no contribution; one that has
+            // not takes at least one, also where P was rounded to just below eps_T (a
+            // contribution leaves T below 1)
+            const float thr = live ? fminf(eps_T / P, 1.0f) : INFINITY;
             float T = 1.0f, C = 0.f;  // C: channel `inst`
             uint32_t last = 0u;
             bool any_alive = false;
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(256, 8) void k_render_fwd(const float* __restrict__
                 if (inst == 0) outLast[(size_t)slot * 256 + p] = last;
             }
             // the walk stopped in this cell: every later cell is neutral here
-            if (T < thr) live = false;
+            live = live && !(T < eps_T / P);
             M = fmaf(P, C, M);
             P *= T;
             if (!any_alive) {

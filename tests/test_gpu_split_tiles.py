@@ -16,6 +16,59 @@ def rast():
     return raster.Rasterizer()
 
 
+def _first_view_equal(alone, batch, px):
+    m = int(alone.bins["counters"][2])
+    assert torch.equal(alone.bins["slot_key"][:m], batch.bins["slot_key"][:m])
+    for a, b, w in ((alone.image, batch.image, 3 * px), (alone.T_final, batch.T_final, px),
+                    (alone.parts["C"], batch.parts["C"], 768 * m), (alone.parts["T"], batch.parts["T"], 256 * m),
+                    (alone.parts["last"], batch.parts["last"], 256 * m)):
+        assert torch.equal(a.view(-1)[:w].view(torch.int32), b.view(-1)[:w].view(torch.int32))
+
+
+def _whole(batch, n_tiles):
+    """Tiles 0 .. n_tiles - 1 of the first view that are not split."""
+    order = batch.bins["tile_order"][: batch.total_tiles].cpu().numpy()
+    assert order.size > SPLIT
+    at = np.empty(order.size, np.int64)
+    at[order] = np.arange(order.size)
+    return at[:n_tiles] >= SPLIT
+
+
+def test_a_pixel_at_the_stop_threshold(rast):
+    """eps_T chosen so that a pixel ends a slot at exactly T = eps_T / P: it has not stopped,
+    but its product P T is rounded to just below eps_T, and the next slot's threshold to
+    above 1.  It takes one contribution there, in a split tile as in a whole one."""
+    W, H, L = 256, 240, 2
+    p = raster.to_device(scenes.scene_uniform(3000, seed=11, D=1, mu_s=-3.0))
+    kd = rast.kd_partition(p, L)
+    cam = scenes.orbit_camera(1.8, 0.3, 0.3, W, H)
+    far = [scenes.orbit_camera(3.0, 0.3 + 0.4 * v, 0.3, W, H) for v in range(15)]  # longer lists
+    tiles = ((W + 15) // 16) * ((H + 15) // 16)
+    assert tiles <= SPLIT
+    whole = _whole(rast.forward(p, kd, [cam] + far, 0.0), tiles)
+    st = rast.forward(p, kd, [cam], 0.0)
+    S = int(st.bins["counters"][2])
+    T = st.parts["T"][: 256 * S].view(S, 256).cpu().numpy()
+    last = st.parts["last"][: 256 * S].view(S, 256).cpu().numpy()
+    tile = st.bins["slot_key"][:S].cpu().numpy() >> L
+    found = []
+    for s in range(S - 1):
+        if s == 0 or tile[s] != tile[s - 1]:
+            P = np.ones(256, np.float32)
+        Pn = P * T[s]
+        eps = np.nextafter(Pn, np.float32(np.inf))
+        if tile[s + 1] == tile[s] and whole[tile[s]]:
+            hit = (eps / P == T[s]) & (Pn < eps) & (last[s + 1] > 0) & (last[s] > 0) & (eps < 1)
+            found += [(s, int(k), float(eps[k])) for k in np.nonzero(hit)[0][:2]]
+        P = Pn
+    assert len(found) >= 4
+    for s, k, eps in found[:: max(len(found) // 6, 1)][:6]:
+        alone = rast.forward(p, kd, [cam], eps)
+        batch = rast.forward(p, kd, [cam] + far, eps)
+        assert int(batch.parts["last"][256 * (s + 1) + k]) > 0
+        _first_view_equal(alone, batch, W * H)
+
+
 def test_a_slot_table_of_some_cells(rast):
     """A caller that renders some of the cells passes a table of their slots, whose
     instances do not follow each other: the same partials as in the whole table
