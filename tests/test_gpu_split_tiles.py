@@ -104,3 +104,28 @@ def test_a_slot_table_of_some_cells(rast):
         bs.slot_key, bs.slot_range, bs.tile_slot = saved
     for k, w in (("C", 768), ("T", 256), ("last", 256)):
         assert torch.equal(own[k][: w * sel.size].view(-1, w), st.parts[k][: w * S].view(S, w)[idx]), k
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5])
+def test_short_lists_split_and_whole(rast, n):
+    """Lists of fewer instances than a group of four, in a split tile and in a whole one."""
+    W, H = 96, 96
+    p = raster.to_device(scenes.scene_uniform(n, seed=n, D=1, mu_s=-0.5))
+    kd = rast.kd_partition(p, 1)
+    cams = [scenes.orbit_camera(3.0, 0.3, 0.3, W, H)] * 16
+    batch = rast.forward(p, kd, cams, 5e-5)
+    alone = rast.forward(p, kd, cams[:1], 5e-5)
+    m = int(alone.bins["counters"][2])
+    held = np.unique(alone.bins["slot_key"][:m].cpu().numpy() >> 1)
+    longest = (alone.bins["slot_range"][: 2 * m].view(m, 2).diff(dim=1)).max().item()
+    assert longest <= n and m > 0
+    order = batch.bins["tile_order"][:SPLIT].cpu().numpy()
+    views = [v for v in range(16) if not np.isin(held + 36 * v, order).all()]
+    assert views  # some view has such a list in a whole tile
+    keys, total = batch.bins["slot_key"], int(batch.bins["counters"][2])
+    assert total == 16 * m
+    for v in views:
+        for k, w in (("C", 768), ("T", 256), ("last", 256)):
+            assert torch.equal(alone.parts[k][: w * m], batch.parts[k][w * m * v: w * m * (v + 1)]), (k, v)
+        assert torch.equal(keys[m * v: m * (v + 1)] - 72 * v, alone.bins["slot_key"][:m])
+        assert torch.equal(alone.image, batch.image[3 * W * H * v: 3 * W * H * (v + 1)])
