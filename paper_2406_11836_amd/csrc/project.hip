@@ -291,10 +291,19 @@ __device__ __forceinline__ bool screen_may_hit(float mu0, float mu1, float mu2, 
 // wave would otherwise run the whole chain for a lane or two.
 static constexpr int PJ_IT = 4;
 
+// Writes the block's list of local indices and returns its length: those kept,
+// in order; or, where most are kept, all of them, the others marked NOT_KEPT: few
+// lanes would be saved, and rows read and written from unaligned starts cost more
+// (4M Gaussians of which 93 % are kept: geometric backward 187 us direct, 214 with
+// every block compacted).
+static constexpr uint32_t NOT_KEPT = 0x8000u;
+
 template <int IT>
-__device__ __forceinline__ int block_compact(const bool* keep, uint16_t* __restrict__ s_list, uint32_t* __restrict__ s_cnt) {
+__device__ __forceinline__ int block_list(const bool* keep, int64_t left, uint16_t* __restrict__ s_list,
+                                          uint32_t* __restrict__ s_cnt) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int all = (int)(left < IT * PJ_THREADS ? left : IT * PJ_THREADS);
     uint64_t b[IT];
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
@@ -312,7 +321,14 @@ __device__ __forceinline__ int block_compact(const bool* keep, uint16_t* __restr
         }
     }
     __syncthreads();
-    return (int)run;
+    if (4 * (int)run < 3 * all) return (int)run;
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const uint32_t at = k * PJ_THREADS + threadIdx.x;
+        s_list[at] = (uint16_t)(keep[k] ? at : at | NOT_KEPT);
+    }
+    __syncthreads();
+    return all;
 }
 
 // The projection of Gaussian i in the views of `scr` (their screen test passed).
@@ -518,12 +534,13 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians 
             s_views[k * PJ_THREADS + threadIdx.x] = (uint16_t)scr;
         }
     }
-    const int m = block_compact<PJ_IT>(keep, s_list, s_cnt);
+    const int m = block_list<PJ_IT>(keep, n - base, s_list, s_cnt);
 #pragma unroll 1
     for (int q = threadIdx.x; q < m; q += PJ_THREADS) {
         int z0 = 0;
         asm volatile("" : "+s"(z0));
         const int loc = s_list[q];
+        if (loc & NOT_KEPT) continue;
         const int64_t i = base + loc;
         project_kept<D>(g, vt, z0, split, center_cell, cells, own_mask, out, i, s_views[loc], g.means[i], g.means[n + i],
                         g.means[2 * n + i], g.log_scales[i], g.log_scales[n + i], g.log_scales[2 * n + i]);
@@ -531,12 +548,14 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians 
 }
 
 // The sparse kernels are taken for large scenes seen by one or two views, where
-// most Gaussians are outside the image (16M-Gaussian city, one 4K view:
-// projection 0.73 -> 0.39 ms, geometric backward 0.61 -> 0.33, SH backward 1.23
-// -> 0.81).  Where most are kept the direct ones are faster: 1M Gaussians, 91%
-// visible: 93 against 117 us, 48 against 56, 77 against 83; so they stay for
-// smaller scenes, and for more views of one scene, which together keep nearly
-// all of it (4M Gaussians, 16 views: geometric backward 1.13 against 1.35 ms).
+// most Gaussians may be outside the image, as in a 16M-Gaussian city at 4K (us,
+// direct / sparse: projection 480 / 387, geometric backward 462 / 329, SH backward
+// 1250 / 808) or a 100M city with cell culling (470 / 330).  What is kept is not known
+// on the host; a block of which most is kept does not compact, so a dense scene
+// pays little (4M clustered, 93 % kept, one view: 319 / 373, 187 / 186, 334 / 331; two
+// views 455 / 520, 255 / 258, 342 / 349).  Smaller scenes take the direct kernels (1M, 91 %
+// visible: projection 93 / 117), and so do more views of one scene, which together
+// keep nearly all of it (4M, 16 views: geometric backward 1.13 / 1.35 ms).
 static bool few_kept(int64_t n, int n_views) { return n >= 2000000 && n_views <= 2; }
 
 template <int D>
@@ -575,17 +594,38 @@ rgs_status project_launch(const rgs_gaussians* g, const ViewTable* vt, const flo
 //
 // Its sparse form takes PJ_IT * 256 Gaussians per block as the projection's
 // does: zeros for those that no view keeps, without reading a parameter, and
-// the adjoint on full waves of the others.
+// the adjoint on full waves of the others, or on all of them in place where
+// most are kept.
 // (z0 as in project_kept.)
-__device__ __forceinline__ void geo_kept(const float* __restrict__ dproj, const rgs_gaussians& g,
-                                         const uint32_t* __restrict__ count, const ViewTable* __restrict__ vt, int z0,
-                                         const rgs_gaussians_grad& out, int64_t i) {
+struct GeoIn {
+    float mu[3], ls[3], q[4], logit;
+};
+__device__ __forceinline__ void geo_load(const rgs_gaussians& g, int64_t i, GeoIn& p) {
+    const int64_t n = g.n;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) p.mu[a] = g.means[a * n + i];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) p.ls[a] = g.log_scales[a * n + i];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) p.q[a] = g.quats[a * n + i];
+    p.logit = g.opacity[i];
+}
+
+// KEPT: some view keeps the Gaussian, and its parameters are loaded here (in this
+// form the compiler keeps their loads together: 47 against 50 us at 1M); else they
+// are in hand, and zeros are written if no view keeps it.
+template <bool KEPT>
+__device__ __forceinline__ void geo_one(const float* __restrict__ dproj, const rgs_gaussians& g, const GeoIn& in,
+                                        const uint32_t* __restrict__ count, const ViewTable* __restrict__ vt, int z0,
+                                        const rgs_gaussians_grad& out, int64_t i) {
     const int64_t n = g.n;
     const int64_t VN = (int64_t)vt->n_views * n;
-    const double mu[3] = {g.means[i], g.means[n + i], g.means[2 * n + i]};
-    const float ls[3] = {g.log_scales[i], g.log_scales[n + i], g.log_scales[2 * n + i]};
-    const double q4[4] = {g.quats[i], g.quats[n + i], g.quats[2 * n + i], g.quats[3 * n + i]};
-    const float logit = g.opacity[i];
+    const double mu[3] = {KEPT ? g.means[i] : in.mu[0], KEPT ? g.means[n + i] : in.mu[1], KEPT ? g.means[2 * n + i] : in.mu[2]};
+    const float ls[3] = {KEPT ? g.log_scales[i] : in.ls[0], KEPT ? g.log_scales[n + i] : in.ls[1],
+                         KEPT ? g.log_scales[2 * n + i] : in.ls[2]};
+    const double q4[4] = {KEPT ? g.quats[i] : in.q[0], KEPT ? g.quats[n + i] : in.q[1], KEPT ? g.quats[2 * n + i] : in.q[2],
+                          KEPT ? g.quats[3 * n + i] : in.q[3]};
+    const float logit = KEPT ? g.opacity[i] : in.logit;
     double gmu[3] = {0.0, 0.0, 0.0};
     float gop = 0.f;
 
@@ -603,10 +643,12 @@ __device__ __forceinline__ void geo_kept(const float* __restrict__ dproj, const 
             S[a][b] = ((Rq[a][0] * s[0]) * (Rq[b][0] * s[0]) + (Rq[a][1] * s[1]) * (Rq[b][1] * s[1])) +
                       (Rq[a][2] * s[2]) * (Rq[b][2] * s[2]);
     double GS[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+    bool any = KEPT;
 
     for (int v = 0; v < vt->n_views; ++v) {
         const int64_t src = (int64_t)v * n + i;
         if (count[src] == 0u) continue;
+        any = true;
         const ViewParams& V = vt->v[v + z0];
         float gd[6];
         for (int c = 0; c < 6; ++c) gd[c] = dproj[c * VN + src];
@@ -675,7 +717,7 @@ __device__ __forceinline__ void geo_kept(const float* __restrict__ dproj, const 
         gop += gd[5] * alpha * (1.f - alpha);
     }
     double gls[3] = {0.0, 0.0, 0.0}, gq[4] = {0.0, 0.0, 0.0, 0.0};
-    {
+    if (any) {
         // S = M M^T with M = Rq diag(s): G_M = 2 G_S M
         double GR[3][3];
         for (int b = 0; b < 3; ++b) {
@@ -721,7 +763,7 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo(const float* __r
     if (i >= g.n) return;
     bool any = false;
     for (int v = 0; v < vt->n_views; ++v) any = any || count[(int64_t)v * g.n + i] != 0u;
-    if (any) geo_kept(dproj, g, count, vt, 0, out, i);
+    if (any) geo_one<true>(dproj, g, GeoIn{}, count, vt, 0, out, i);
     else geo_zero(out, g.n, i);
 }
 
@@ -743,37 +785,51 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo_sparse(const flo
             if (i < n && count[(int64_t)v * n + i] != 0u) keep[k] = true;
         }
     }
+    // zeros where few of a wave are kept, before the wait for the list; elsewhere after
+    // it, and only if the list leaves the others out (with them in it their zeros go
+    // into the lines that the kept ones write: 184 us instead of 197 at 4M, 93 % kept)
+    uint32_t late = 0;
 #pragma unroll
     for (int k = 0; k < PJ_IT; ++k) {
         const int64_t i = base + k * PJ_THREADS + threadIdx.x;
-        if (i < n && !keep[k]) geo_zero(out, n, i);
+        if (__popcll(__ballot(keep[k])) >= 48) late |= 1u << k;
+        else if (i < n && !keep[k]) geo_zero(out, n, i);
     }
-    const int m = block_compact<PJ_IT>(keep, s_list, s_cnt);
+    const int m = block_list<PJ_IT>(keep, n - base, s_list, s_cnt);
+    if (late && m < n - base && m < PJ_IT * PJ_THREADS) {
+#pragma unroll
+        for (int k = 0; k < PJ_IT; ++k) {
+            const int64_t i = base + k * PJ_THREADS + threadIdx.x;
+            if (((late >> k) & 1u) && i < n && !keep[k]) geo_zero(out, n, i);
+        }
+    }
+    // the next Gaussian's parameters are loaded ahead
+    GeoIn p;
+    if ((int)threadIdx.x < m) geo_load(g, base + (s_list[threadIdx.x] & (NOT_KEPT - 1u)), p);
 #pragma unroll 1
     for (int q = threadIdx.x; q < m; q += PJ_THREADS) {
         int z0 = 0;
         asm volatile("" : "+s"(z0));
-        geo_kept(dproj, g, count, vt, z0, out, base + s_list[q]);
+        const int64_t i = base + (s_list[q] & (NOT_KEPT - 1u));
+        const GeoIn now = p;
+        if (q + PJ_THREADS < m) geo_load(g, base + (s_list[q + PJ_THREADS] & (NOT_KEPT - 1u)), p);
+        geo_one<false>(dproj, g, now, count, vt, z0, out, i);
     }
 }
 
 // SH colour part: gradients of the SH coefficients, and the view-direction
 // share of the mean gradient added to what the geometric kernel wrote.
+// FEW (of a large scene's Gaussians may be kept): a Gaussian that no view keeps gets
+// zeros without its coefficients being read; else the coefficients are loaded
+// before the counts are known.  (Four Gaussians per thread in turn, their counts
+// first, take 356 us instead of 333 at 4M.)
 template <int D, bool FEW>
-__global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_sh(const float* __restrict__ dproj, rgs_gaussians g,
-                                                               const uint32_t* __restrict__ count,
-                                                               const ViewTable* __restrict__ vt,
-                                                               rgs_gaussians_grad out) {
+__device__ __forceinline__ void sh_one(const float* __restrict__ dproj, const rgs_gaussians& g,
+                                       const uint32_t* __restrict__ count, const ViewTable* __restrict__ vt,
+                                       const rgs_gaussians_grad& out, int64_t i, bool any) {
     const int64_t n = g.n;
-    const int64_t i = (int64_t)blockIdx.x * PJ_THREADS + threadIdx.x;
-    if (i >= n) return;
     constexpr int nc = (D + 1) * (D + 1);
     const int64_t VN = (int64_t)vt->n_views * n;
-    // FEW: a Gaussian that no view keeps gets zeros without its coefficients
-    // being read; else the coefficients are loaded before the counts are known
-    bool any = false;
-    if (FEW)
-        for (int v = 0; v < vt->n_views; ++v) any = any || count[(int64_t)v * n + i] != 0u;
     float mu[3] = {0.f, 0.f, 0.f};
     float gmu[3] = {0.f, 0.f, 0.f};
     float gsh[3 * nc], fsh[3 * nc];
@@ -823,6 +879,20 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_sh(const float* __re
         for (int a = 0; a < 3; ++a) out.means[a * n + i] += gmu[a];
 #pragma unroll
     for (int k = 0; k < 3 * nc; ++k) out.sh[(int64_t)k * n + i] = gsh[k];
+}
+
+template <int D, bool FEW>
+__global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_sh(const float* __restrict__ dproj, rgs_gaussians g,
+                                                               const uint32_t* __restrict__ count,
+                                                               const ViewTable* __restrict__ vt,
+                                                               rgs_gaussians_grad out) {
+    const int64_t n = g.n;
+    const int64_t i = (int64_t)blockIdx.x * PJ_THREADS + threadIdx.x;
+    if (i >= n) return;
+    bool any = false;
+    if (FEW)
+        for (int v = 0; v < vt->n_views; ++v) any = any || count[(int64_t)v * n + i] != 0u;
+    sh_one<D, FEW>(dproj, g, count, vt, out, i, any);
 }
 
 template <int D>

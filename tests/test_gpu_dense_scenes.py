@@ -1,0 +1,47 @@
+"""Large scenes in one or two views: the kernels' blocks compact what they keep, or take
+all in place where that is most of it; against the kernels of more views."""
+import pytest
+import torch
+
+from paper_2406_11836_amd import raster, scenes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,radius,grouped,lo,hi", [
+    (3, 2.4, False, 0.85, 0.99),  # nearly every block in place
+    (1, 1.2, False, 0.3, 0.7),    # every block compacts
+    (0, 1.0, True, 0.1, 0.9),     # whole, partial and empty blocks
+])
+def test_blocks_in_place_and_compacted(D, radius, grouped, lo, hi):
+    """One view and the same view among three (the others' image gradients zero) have
+    the same records, image and gradients, bit for bit."""
+    n, W, H = 2_000_137, 400, 300
+    r = raster.Rasterizer()
+    g = torch.Generator("cuda").manual_seed(D)
+    f = dict(device="cuda", generator=g)
+    p = dict(means=torch.rand((3, n), **f) * 2 - 1, log_scales=torch.randn((3, n), **f) * 0.3 - 5.5,
+             quats=torch.randn((4, n), **f), opacity=torch.randn((n,), **f),
+             sh=torch.randn((3 * (D + 1) ** 2, n), **f) * 0.3, sh_degree=D)
+    if grouped:
+        p, _ = r.group_by_cell(p, r.kd_partition(p, 5))
+    kd = r.kd_partition(p, 2)
+    cams = [scenes.orbit_camera(radius, 0.3 + v, 0.3, W, H) for v in range(3)]
+    a = r.forward(p, kd, cams[:1], 5e-5)
+    b = r.forward(p, kd, cams, 5e-5)
+    kept = a.proj["count"][:n] != 0
+    assert lo < kept.float().mean().item() < hi
+    blocks = torch.nn.functional.pad(kept.float(), (0, 1024 - n % 1024)).view(-1, 1024).mean(1)[:-1]
+    if grouped:
+        assert (blocks >= 0.75).any() and (blocks == 0).any() and ((blocks > 0.2) & (blocks < 0.7)).any()
+    assert torch.equal(a.proj["count"][:n], b.proj["count"][:n])
+    for key, w in (("rec", 16), ("bin", 8), ("depth", 1)):
+        x, y = (s.proj[key][: n * w].view(n, w)[kept].view(torch.int32) for s in (a, b))
+        assert torch.equal(x, y), key
+    assert torch.equal(a.image, b.image[: 3 * W * H])
+    d = torch.randn(3 * W * H, **f)
+    ga = r.backward(a, p, d)
+    gb = r.backward(b, p, torch.cat([d, torch.zeros(6 * W * H, device="cuda")]))
+    for k in raster.PARAM_KEYS:
+        assert torch.equal(ga[k], gb[k]) and torch.count_nonzero(ga[k]) > 0, k
+        assert torch.count_nonzero(ga[k][..., ~kept]) == 0, k
