@@ -284,12 +284,11 @@ __device__ __forceinline__ bool screen_may_hit(float mu0, float mu1, float mu2, 
 // the leaf of the centre only, with no indicator test in the render (flag
 // bit 0 set: the render takes every pixel of the footprint for that cell).
 //
-// A block of the sparse kernel takes PJ_IT * 256 consecutive Gaussians in two phases: the screen test
+// A block of the sparse kernel takes IT * 256 consecutive Gaussians in two phases: the screen test
 // of each (cheap, coalesced), the survivors compacted in order in LDS, and
 // the fp64 chain and colours on full waves of survivors.  Where a few in a
 // hundred Gaussians reach the image (a city, an unsorted scene) nearly every
 // wave would otherwise run the whole chain for a lane or two.
-static constexpr int PJ_IT = 4;
 
 // Writes the block's list of local indices and returns its length: those kept,
 // in order; or, where most are kept, all of them, the others marked NOT_KEPT: few
@@ -484,35 +483,35 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project(rgs_gaussians g, cons
     project_kept<D>(g, vt, 0, split, center_cell, cells, own_mask, out, i, scr, mu[0], mu[1], mu[2], ls[0], ls[1], ls[2]);
 }
 
-template <int D>
+template <int D, int IT>
 __global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians g, const ViewTable* __restrict__ vt,
                                                         const float* __restrict__ split,
                                                         const int32_t* __restrict__ center_cell, int cells,
                                                         const uint32_t* __restrict__ own_mask, rgs_projected out) {
-    __shared__ uint16_t s_list[PJ_IT * PJ_THREADS];
-    __shared__ uint16_t s_views[PJ_IT * PJ_THREADS];  // views whose screen test passes
-    __shared__ uint32_t s_cnt[PJ_IT * 4];
+    __shared__ uint16_t s_list[IT * PJ_THREADS];
+    __shared__ uint16_t s_views[IT * PJ_THREADS];  // views whose screen test passes
+    __shared__ uint32_t s_cnt[IT * 4];
     const int64_t n = g.n;
-    const int64_t base = (int64_t)blockIdx.x * (PJ_IT * PJ_THREADS);
-    bool keep[PJ_IT];
+    const int64_t base = (int64_t)blockIdx.x * (IT * PJ_THREADS);
+    bool keep[IT];
     {
-        uint32_t view_ok[PJ_IT];
+        uint32_t view_ok[IT];
 #pragma unroll
-        for (int k = 0; k < PJ_IT; ++k) view_ok[k] = (1u << vt->n_views) - 1u;
+        for (int k = 0; k < IT; ++k) view_ok[k] = (1u << vt->n_views) - 1u;
         if (vt->culled) {
-            int cell[PJ_IT];
+            int cell[IT];
 #pragma unroll
-            for (int k = 0; k < PJ_IT; ++k) {
+            for (int k = 0; k < IT; ++k) {
                 const int64_t i = base + k * PJ_THREADS + threadIdx.x;
                 cell[k] = center_cell[i < n ? i : n - 1];
             }
 #pragma unroll
-            for (int k = 0; k < PJ_IT; ++k) view_ok[k] = cell_views(vt, cell[k]);
+            for (int k = 0; k < IT; ++k) view_ok[k] = cell_views(vt, cell[k]);
         }
         // all loads of the thread before their use
-        float mu[PJ_IT][3], ls[PJ_IT][3];
+        float mu[IT][3], ls[IT][3];
 #pragma unroll
-        for (int k = 0; k < PJ_IT; ++k) {
+        for (int k = 0; k < IT; ++k) {
             const int64_t i = base + k * PJ_THREADS + threadIdx.x;
             if (i >= n) view_ok[k] = 0u;
             if (view_ok[k] == 0u) continue;
@@ -523,7 +522,7 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians 
             }
         }
 #pragma unroll
-        for (int k = 0; k < PJ_IT; ++k) {
+        for (int k = 0; k < IT; ++k) {
             const int64_t i = base + k * PJ_THREADS + threadIdx.x;
             keep[k] = false;
             if (i >= n) continue;
@@ -534,7 +533,7 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians 
             s_views[k * PJ_THREADS + threadIdx.x] = (uint16_t)scr;
         }
     }
-    const int m = block_list<PJ_IT>(keep, n - base, s_list, s_cnt);
+    const int m = block_list<IT>(keep, n - base, s_list, s_cnt);
 #pragma unroll 1
     for (int q = threadIdx.x; q < m; q += PJ_THREADS) {
         int z0 = 0;
@@ -549,11 +548,11 @@ __global__ __launch_bounds__(PJ_THREADS, 3) void k_project_sparse(rgs_gaussians 
 
 // The sparse kernels are taken for large scenes seen by one or two views, where
 // most Gaussians may be outside the image, as in a 16M-Gaussian city at 4K (us,
-// direct / sparse: projection 480 / 387, geometric backward 462 / 329, SH backward
+// direct / sparse: projection 480 / 357, geometric backward 462 / 327, SH backward
 // 1250 / 808) or a 100M city with cell culling (470 / 330).  What is kept is not known
 // on the host; a block of which most is kept does not compact, so a dense scene
-// pays little (4M clustered, 93 % kept, one view: 319 / 373, 187 / 186, 334 / 331; two
-// views 455 / 520, 255 / 258, 342 / 349).  Smaller scenes take the direct kernels (1M, 91 %
+// pays little (4M clustered, 93 % kept, one view: 319 / 348, 187 / 185, 334 / 331; two
+// views 455 / 486, 255 / 258, 342 / 349).  Smaller scenes take the direct kernels (1M, 91 %
 // visible: projection 93 / 117), and so do more views of one scene, which together
 // keep nearly all of it (4M, 16 views: geometric backward 1.13 / 1.35 ms).
 static bool few_kept(int64_t n, int n_views) { return n >= 2000000 && n_views <= 2; }
@@ -561,12 +560,20 @@ static bool few_kept(int64_t n, int n_views) { return n >= 2000000 && n_views <=
 template <int D>
 static void project_one(const rgs_gaussians* g, const ViewTable* vt, const float* split, const int32_t* center_cell, int cells,
                         const uint32_t* own_mask, const rgs_projected* out, int n_views, hipStream_t s) {
-    if (few_kept(g->n, n_views))
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project_sparse<D>), dim3((unsigned)((g->n + PJ_IT * PJ_THREADS - 1) / (PJ_IT * PJ_THREADS))),
-                           dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells, own_mask, *out);
+    // Two Gaussians per thread, so that a scene of a few million is many rounds of blocks
+    // (1280 are resident; with four and with two, us: 4M clustered 374 / 345, 16M city 387 / 358); four
+    // from 32M on, where most blocks only find that they have none, and what they
+    // wait for is a load per thread (100M city, culled: 371 with two, 330 with four).
+    const unsigned blocks = (unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS);
+    if (few_kept(g->n, n_views) && g->n < 32000000)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project_sparse<D, 2>), dim3((blocks + 1) / 2), dim3(PJ_THREADS), 0, s, *g, vt,
+                           split, center_cell, cells, own_mask, *out);
+    else if (few_kept(g->n, n_views))
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project_sparse<D, 4>), dim3((blocks + 3) / 4), dim3(PJ_THREADS), 0, s, *g, vt,
+                           split, center_cell, cells, own_mask, *out);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project<D>), dim3((unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS)),
-                           dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell, cells, own_mask, *out);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_project<D>), dim3(blocks), dim3(PJ_THREADS), 0, s, *g, vt, split, center_cell,
+                           cells, own_mask, *out);
 }
 
 rgs_status project_launch(const rgs_gaussians* g, const ViewTable* vt, const float* split, const int32_t* center_cell,
@@ -592,11 +599,13 @@ rgs_status project_launch(const rgs_gaussians* g, const ViewTable* vt, const flo
 // it and adds its share of the mean gradient (the view direction).  Split,
 // each kernel keeps fewer registers live than one kernel doing both.
 //
-// Its sparse form takes PJ_IT * 256 Gaussians per block as the projection's
+// Its sparse form takes GE_IT * 256 Gaussians per block as the projection's
 // does: zeros for those that no view keeps, without reading a parameter, and
 // the adjoint on full waves of the others, or on all of them in place where
 // most are kept.
 // (z0 as in project_kept.)
+static constexpr int GE_IT = 4;
+
 struct GeoIn {
     float mu[3], ls[3], q[4], logit;
 };
@@ -771,16 +780,16 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo_sparse(const flo
                                                                        const uint32_t* __restrict__ count,
                                                                        const ViewTable* __restrict__ vt,
                                                                        rgs_gaussians_grad out) {
-    __shared__ uint16_t s_list[PJ_IT * PJ_THREADS];
-    __shared__ uint32_t s_cnt[PJ_IT * 4];
+    __shared__ uint16_t s_list[GE_IT * PJ_THREADS];
+    __shared__ uint32_t s_cnt[GE_IT * 4];
     const int64_t n = g.n;
-    const int64_t base = (int64_t)blockIdx.x * (PJ_IT * PJ_THREADS);
-    bool keep[PJ_IT];
+    const int64_t base = (int64_t)blockIdx.x * (GE_IT * PJ_THREADS);
+    bool keep[GE_IT];
 #pragma unroll
-    for (int k = 0; k < PJ_IT; ++k) keep[k] = false;
+    for (int k = 0; k < GE_IT; ++k) keep[k] = false;
     for (int v = 0; v < vt->n_views; ++v) {
 #pragma unroll
-        for (int k = 0; k < PJ_IT; ++k) {
+        for (int k = 0; k < GE_IT; ++k) {
             const int64_t i = base + k * PJ_THREADS + threadIdx.x;
             if (i < n && count[(int64_t)v * n + i] != 0u) keep[k] = true;
         }
@@ -790,15 +799,15 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project_bwd_geo_sparse(const flo
     // into the lines that the kept ones write: 184 us instead of 197 at 4M, 93 % kept)
     uint32_t late = 0;
 #pragma unroll
-    for (int k = 0; k < PJ_IT; ++k) {
+    for (int k = 0; k < GE_IT; ++k) {
         const int64_t i = base + k * PJ_THREADS + threadIdx.x;
         if (__popcll(__ballot(keep[k])) >= 48) late |= 1u << k;
         else if (i < n && !keep[k]) geo_zero(out, n, i);
     }
-    const int m = block_list<PJ_IT>(keep, n - base, s_list, s_cnt);
-    if (late && m < n - base && m < PJ_IT * PJ_THREADS) {
+    const int m = block_list<GE_IT>(keep, n - base, s_list, s_cnt);
+    if (late && m < n - base && m < GE_IT * PJ_THREADS) {
 #pragma unroll
-        for (int k = 0; k < PJ_IT; ++k) {
+        for (int k = 0; k < GE_IT; ++k) {
             const int64_t i = base + k * PJ_THREADS + threadIdx.x;
             if (((late >> k) & 1u) && i < n && !keep[k]) geo_zero(out, n, i);
         }
@@ -912,7 +921,7 @@ rgs_status project_bwd_launch(const float* dproj, const rgs_gaussians* g, const 
     const unsigned grid = (unsigned)((g->n + PJ_THREADS - 1) / PJ_THREADS);
     const bool few = few_kept(g->n, n_views);
     if (few)
-        hipLaunchKernelGGL(k_project_bwd_geo_sparse, dim3((grid + PJ_IT - 1) / PJ_IT), dim3(PJ_THREADS), 0, s, dproj, *g,
+        hipLaunchKernelGGL(k_project_bwd_geo_sparse, dim3((grid + GE_IT - 1) / GE_IT), dim3(PJ_THREADS), 0, s, dproj, *g,
                            count, vt, *out);
     else
         hipLaunchKernelGGL(k_project_bwd_geo, dim3(grid), dim3(PJ_THREADS), 0, s, dproj, *g, count, vt,

@@ -8,19 +8,20 @@ from paper_2406_11836_amd import raster, scenes
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,radius,grouped,lo,hi", [
-    (3, 2.4, False, 0.85, 0.99),  # nearly every block in place
-    (1, 1.2, False, 0.3, 0.7),    # every block compacts
-    (0, 1.0, True, 0.1, 0.9),     # whole, partial and empty blocks
+@pytest.mark.parametrize("n,D,radius,grouped,lo,hi", [
+    (2_000_137, 3, 2.4, False, 0.85, 0.99),  # nearly every block in place
+    (2_000_137, 1, 1.2, False, 0.3, 0.7),    # every block compacts
+    (2_000_137, 0, 1.0, True, 0.1, 0.9),     # whole, partial and empty blocks
+    (32_000_137, 0, 1.0, True, 0.1, 0.9),    # the projection's four Gaussians per thread
 ])
-def test_blocks_in_place_and_compacted(D, radius, grouped, lo, hi):
+def test_blocks_in_place_and_compacted(n, D, radius, grouped, lo, hi):
     """One view and the same view among three (the others' image gradients zero) have
     the same records, image and gradients, bit for bit."""
-    n, W, H = 2_000_137, 400, 300
+    W, H = 400, 300
     r = raster.Rasterizer()
     g = torch.Generator("cuda").manual_seed(D)
     f = dict(device="cuda", generator=g)
-    p = dict(means=torch.rand((3, n), **f) * 2 - 1, log_scales=torch.randn((3, n), **f) * 0.3 - 5.5,
+    p = dict(means=torch.rand((3, n), **f) * 2 - 1, log_scales=torch.randn((3, n), **f) * 0.3 - (5.5 if n < 8_000_000 else 6.5),
              quats=torch.randn((4, n), **f), opacity=torch.randn((n,), **f),
              sh=torch.randn((3 * (D + 1) ** 2, n), **f) * 0.3, sh_degree=D)
     if grouped:
