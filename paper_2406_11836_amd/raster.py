@@ -42,49 +42,63 @@ def _stream():
 
 
 class Carved(dict):
-    """Named tensors in one allocation; each is made when it is first asked for."""
+    """Named tensors in one allocation; each is made when it is first asked for, and
+    all of them before anything but a lookup, which then is the dictionary's own."""
 
     def __init__(self, base, at):
         super().__init__()
-        self._base, self._at = base, at
+        self._base, self._at = base, at  # _at: None once all are made
 
     def ptr(self, key):
         t = dict.get(self, key)
-        return self._base.data_ptr() + self._at[key][0] if t is None else t.data_ptr()
+        if t is None and self._at is not None and key in self._at:
+            return self._base.data_ptr() + self._at[key][0]
+        return self[key].data_ptr()
 
     def __missing__(self, key):
+        if self._at is None or key not in self._at:
+            raise KeyError(key)
         off, n, dtype = self._at[key]
         t = self._base[off: off + n * _SIZE[dtype]].view(dtype)
         dict.__setitem__(self, key, t)
         return t
 
-    def __setitem__(self, key, t):
-        self._at.setdefault(key, None)
-        dict.__setitem__(self, key, t)
+    def _all(self):
+        if self._at is not None:
+            made = {k: self[k] for k in self._at}
+            self._at = None
+            dict.clear(self)
+            dict.update(self, made)  # in the buffers' order
+        return self
 
-    def _full(self):
-        return {k: self[k] for k in self._at}
+    def copy(self):
+        return dict(self.items())
 
-    def get(self, key, default=None):
-        return self[key] if key in self._at else default
+    __copy__ = copy
 
-    def keys(self):
-        return self._full().keys()
+    def __reduce_ex__(self, protocol):  # as separate buffers, without the rest of the allocation
+        return dict, ({k: t.clone() if isinstance(t, torch.Tensor) else t for k, t in self.items()},)
 
-    def values(self):
-        return self._full().values()
+    def __or__(self, other):
+        return self.copy() | dict(other) if isinstance(other, dict) else NotImplemented
 
-    def items(self):
-        return self._full().items()
+    def __ror__(self, other):
+        return dict(other) | self.copy() if isinstance(other, dict) else NotImplemented
 
-    def __iter__(self):
-        return iter(self._full())
 
-    def __len__(self):
-        return len(self._at)
+def _whole(name):
+    method = getattr(dict, name)
 
-    def __contains__(self, key):
-        return key in self._at
+    def f(self, *args, **kw):
+        return method(self._all(), *(a._all() if isinstance(a, Carved) else a for a in args), **kw)
+    f.__name__ = name
+    return f
+
+
+for _name in ("__setitem__", "__delitem__", "__contains__", "__iter__", "__len__", "__reversed__", "__repr__", "__eq__",
+              "__ne__", "__ior__", "get", "keys", "values", "items", "pop", "popitem", "setdefault", "update", "clear"):
+    setattr(Carved, _name, _whole(_name))
+Carved.__hash__ = None
 
 
 def _ptr(d, key):
