@@ -37,8 +37,16 @@ def _p(t):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without a Stream object (a microsecond or two per call).
+# The two names are not public: a torch without them is asked the public way.
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_DEVICE = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _RAW_STREAM is None or _DEVICE is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _RAW_STREAM(_DEVICE())
 
 
 class Carved(dict):

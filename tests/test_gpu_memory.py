@@ -69,3 +69,15 @@ def test_gradients_with_either_workspace(monkeypatch, n, mu, W, H, views, L, out
     for a, b in zip(*got):
         assert torch.equal(a, b)
         assert out or n == 1 or torch.count_nonzero(a) > 0
+
+
+def test_stream_handle(monkeypatch):
+    """The current stream's handle, also where torch lacks the direct way to it."""
+    side = torch.cuda.Stream()
+    for names in ({}, {"_RAW_STREAM": None}, {"_DEVICE": None}):
+        with monkeypatch.context() as m:
+            for k, v in names.items():
+                m.setattr(raster, k, v)
+            assert raster._stream() == torch.cuda.current_stream().cuda_stream
+            with torch.cuda.stream(side):
+                assert raster._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
