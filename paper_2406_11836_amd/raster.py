@@ -15,7 +15,7 @@ arguments and owns buffers.
 from __future__ import annotations
 
 import ctypes as C
-from dataclasses import dataclass, field
+from dataclasses import dataclass, field, replace
 
 import numpy as np
 import torch
@@ -482,7 +482,9 @@ class RetinaRasterize(torch.autograd.Function):
         params = dict(means=means.contiguous(), log_scales=log_scales.contiguous(), quats=quats.contiguous(),
                       opacity=opacity.contiguous(), sh=sh.contiguous(), sh_degree=sh_degree)
         st = rast.forward(params, kd, cams, eps_T)
-        ctx.st, ctx.rast, ctx.params = st, rast, params
+        # without the outputs: an output that its own node holds is never freed, and with it
+        # all the buffers of the pass
+        ctx.st, ctx.rast, ctx.params = replace(st, image=None, T_final=None), rast, params
         return st.image, st.T_final
 
     @staticmethod

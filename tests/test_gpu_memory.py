@@ -81,3 +81,26 @@ def test_stream_handle(monkeypatch):
             assert raster._stream() == torch.cuda.current_stream().cuda_stream
             with torch.cuda.stream(side):
                 assert raster._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+
+
+@pytest.mark.parametrize("backward", [True, False])
+def test_autograd_passes_free_their_buffers(backward):
+    """A pass through torch's autograd leaves nothing on the device once its outputs are
+    dropped, whether it was differentiated or not."""
+    r = raster.Rasterizer()
+    p = _scene(3000, -3.0)
+    for k in raster.PARAM_KEYS:
+        p[k].requires_grad_(True)
+    kd = r.kd_partition(p, 2)
+    cam = scenes.orbit_camera(3.0, 0.3, 0.3, 96, 64)
+    sizes = []
+    for _ in range(8):
+        for k in raster.PARAM_KEYS:
+            p[k].grad = None
+        image, T = raster.rasterize(p, [cam], kd, r)
+        if backward:
+            (image.sum() + T.sum()).backward()
+            assert all(p[k].grad is not None for k in raster.PARAM_KEYS)
+        del image, T
+        sizes.append(torch.cuda.memory_allocated())
+    assert sizes[-1] == sizes[2]
