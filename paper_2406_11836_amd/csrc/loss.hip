@@ -220,10 +220,6 @@ __global__ __launch_bounds__(LF_THREADS) void k_loss_final(const P2* __restrict_
     loss_final_sums<LF_THREADS, P2>(part, nb, invN, w, loss, s_a, s_b);
 }
 
-// What callers size their workspaces by (a fixed array's largest view among
-// them): three maps of the image and 3.1 pairs of sums per 512 values, of which the
-// sums are used.
-
 // Backward: convolve the three derivative maps with the (symmetric) window
 // and combine: dL/dx = sign(x - y)/N + sc (w*g_mu + 2 x w*g_xx + y w*g_xy).
 // Block 0 adds up the forward's block partials into the loss (dispatched
@@ -529,17 +525,23 @@ __global__ __launch_bounds__(SC, 3) void k_ssim(const float* __restrict__ x, con
     if (t < 2) part[2 * b + t] = s_w[0][t] + s_w[1][t];
 }
 
-// One marching pass from SSIM_MARCH values on, where the strips fit the width
-// (at most a quarter of them beyond it): us for the loss, tiles / marching:
-// 1600x1060 76 / 79, 1920x1080 91 / 86, 2000x1200 112 / 92, 2560x1440 162 / 128, 3840x2160 367 / 236,
-// 5000x3000 644 / 415; a quarter of the strips' time on the chip is start-up at
-// smaller views (997x663: 36 / 54), and 130 columns take two strips (125 / 138 at
-// 20000 rows).  Segments are as long as one round of blocks
-// allows (3 waves per SIMD: 6 blocks per CU), since each computes ten rows
-// above and below its own: 2048 blocks, two rounds, take 302 us at 3840x2160.
-static constexpr int64_t SSIM_MARCH = 6000000;
+// One marching pass from SSIM_MARCH values on, where its blocks' rows take less time
+// than tiles.  Segments are as long as one round of blocks allows (3 waves per SIMD:
+// 6 blocks per CU), since each computes ten rows above and below its own: 2048
+// blocks, two rounds, take 302 us at 3840x2160.  So the pass takes 1.4 us per row of
+// a segment and its halo, whatever the shape, and the tiles 12.8 us per million
+// values: SSIM_ROW_VALUES values per row.  us for the loss, tiles / marching:
+// 1920x1080 81 / 78, 2000x1200 93 / 84, 2560x1440 139 / 117, 3840x2160 347 / 230, 5000x3000
+// 622 / 413, 60000x100 271 / 167, 236x20000 202 / 139; few rows or strips that go far
+// beyond the width leave blocks or columns idle: 20901x131 112 / 121, 20500x100 88 / 99,
+// 7000x300 81 / 84, 130x20000 125 / 138.  Smaller views (1600x1060 76 / 79, 997x663 36 / 54)
+// are mostly the pass's start-up.
+static constexpr int64_t SSIM_MARCH = 6000000, SSIM_ROW_VALUES = 109000;
 static constexpr int SSIM_BLOCKS = 1536, SSIM_ROWS = 32;
 
+// What callers size their workspaces by (a fixed array's largest view among
+// them): three maps of the image and 3.1 pairs of sums per 512 values, of which the
+// sums are used.
 size_t loss_ws_bytes(int H, int W) {
     const int64_t m = 3 * (int64_t)H * W;
     const int64_t nb = (m + LS_THREADS - 1) / LS_THREADS;
@@ -562,14 +564,14 @@ rgs_status loss_launch(const float* image, const float* target, int H, int W, fl
     for (int k = 0; k < 11; ++k) { g[k] = exp(-((k - 5) * (k - 5)) / (2.0 * 1.5 * 1.5)); gs += g[k]; }
     for (int k = 0; k < 11; ++k) win.w[k] = (float)(g[k] / gs);
     const int strips = (W + SO - 1) / SO;
+    const int most = SSIM_BLOCKS / (3 * strips) > 1 ? SSIM_BLOCKS / (3 * strips) : 1;  // segments
+    int rows = (H + most - 1) / most;
+    if (rows < SSIM_ROWS) rows = SSIM_ROWS;
     if (ssim_w == 0.f) {
         hipLaunchKernelGGL(k_l1_only, dim3((unsigned)nb), dim3(LS_THREADS), 0, s, image, target, m, invN, dimg, part);
         hipLaunchKernelGGL(k_loss_final<float2>, dim3(1), dim3(LF_THREADS), 0, s, reinterpret_cast<const float2*>(part),
                            (int)nb, invN, ssim_w, loss);
-    } else if (m >= SSIM_MARCH && (int64_t)strips * SO * 4 <= (int64_t)W * 5) {
-        const int most = SSIM_BLOCKS / (3 * strips) > 1 ? SSIM_BLOCKS / (3 * strips) : 1;
-        int rows = (H + most - 1) / most;
-        if (rows < SSIM_ROWS) rows = SSIM_ROWS;
+    } else if (m >= SSIM_MARCH && (rows + 4 * HALO) * SSIM_ROW_VALUES <= m) {
         const int segs = (H + rows - 1) / rows;
         double* sums = reinterpret_cast<double*>(ws);  // (no derivative maps here)
         hipLaunchKernelGGL(k_ssim, dim3((unsigned)(3 * strips * segs)), dim3(SC), 0, s, image, target, H, W, win, strips,
