@@ -117,40 +117,65 @@ struct PermOut {
 // last-level cache holds, instead of from all 59 at once: each random 4-byte
 // read moves a line, mostly from that cache and not from HBM.  59 rows of a
 // random permutation: 22.8 -> 16.9 ms at 16M Gaussians, 1.00 -> 0.43 ms at 1M.
-static constexpr int PM_ITEMS = 4;
+// Where neighbours mostly come from neighbours (a scene regrouped after it was
+// grouped) there is no line to save, and reading the permutation for each row
+// costs half as much again as the rows: there the first PM_SUB rows' blocks move
+// all rows, each of a part of its tile, and the others end (59 rows, 4M: 400 us with all
+// rows by one thread each, 536 row by row, 407 so; 1M 101, 132, 109; 16M 1590, 2241,
+// 1580).  A random permutation takes 3 to 8 % longer for the question.  Tiles of 8
+// steps from 8M on, where a row is beyond the L2 anyway, so that few blocks end.
+static constexpr int PM_ITEMS = 4, PM_SUB = 4;
+static constexpr int PM_STEP = TR_THREADS * PM_ITEMS;  // a tile is `steps` of them
+static constexpr int64_t PM_NEAR = 262144;  // below, latency is what counts: row by row (100k: 13 us, all rows 19)
 
-__global__ __launch_bounds__(TR_THREADS) void k_permute(rgs_gaussians in, PermOut out, const int32_t* __restrict__ perm) {
-    const int64_t n = in.n;
-    const int r = blockIdx.y;
-    const float* src;
-    float* dst;
-    if (r < 3) { src = in.means + r * n; dst = out.means + r * n; }
-    else if (r < 6) { src = in.log_scales + (r - 3) * n; dst = out.log_scales + (r - 3) * n; }
-    else if (r < 10) { src = in.quats + (r - 6) * n; dst = out.quats + (r - 6) * n; }
-    else if (r == 10) { src = in.opacity; dst = out.opacity; }
-    else { src = in.sh + (r - 11) * n; dst = out.sh + (r - 11) * n; }
-    const int64_t base = (int64_t)blockIdx.x * (TR_THREADS * PM_ITEMS) + threadIdx.x;
-    int64_t s[PM_ITEMS];
-    float v[PM_ITEMS];
+__global__ __launch_bounds__(TR_THREADS) void k_permute(rgs_gaussians in, PermOut out, int rows, int steps,
+                                                        const int32_t* __restrict__ perm) {
+    const int64_t n = in.n, tile = (int64_t)blockIdx.x * steps * PM_STEP;
+    if (n >= PM_NEAR && perm_mostly_near(perm, n)) {
+        if (blockIdx.y >= PM_SUB) return;
+        for (int k = 0; k < steps; ++k) {
+            const int64_t j = tile + (int64_t)(blockIdx.y * steps + k) * TR_THREADS + threadIdx.x;
+            const int64_t s = j < n ? perm[j] : -1;
+            if (s < 0 || s >= n) continue;
+            constexpr int U = 8;  // loads in flight
+            for (int r0 = 0; r0 < rows; r0 += U) {
+                float v[U];
 #pragma unroll
-    for (int k = 0; k < PM_ITEMS; ++k) {
-        const int64_t j = base + k * TR_THREADS;
-        s[k] = j < n ? perm[j] : -1;
+                for (int u = 0; u < U; ++u) v[u] = r0 + u < rows ? param_row(in, n, r0 + u)[s] : 0.f;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (r0 + u < rows) param_row(out, n, r0 + u)[j] = v[u];
+            }
+        }
+        return;
     }
+    const float* src = param_row(in, n, blockIdx.y);
+    float* dst = param_row(out, n, blockIdx.y);
+    for (int k = 0; k < steps; ++k) {
+        const int64_t at = tile + (int64_t)k * PM_STEP + threadIdx.x;
+        int64_t s[PM_ITEMS];
+        float v[PM_ITEMS];
 #pragma unroll
-    for (int k = 0; k < PM_ITEMS; ++k) v[k] = (s[k] >= 0 && s[k] < n) ? src[s[k]] : 0.f;
+        for (int u = 0; u < PM_ITEMS; ++u) {
+            const int64_t j = at + u * TR_THREADS;
+            s[u] = j < n ? perm[j] : -1;
+        }
 #pragma unroll
-    for (int k = 0; k < PM_ITEMS; ++k)
-        if (s[k] >= 0 && s[k] < n) dst[base + k * TR_THREADS] = v[k];
+        for (int u = 0; u < PM_ITEMS; ++u) v[u] = (s[u] >= 0 && s[u] < n) ? src[s[u]] : 0.f;
+#pragma unroll
+        for (int u = 0; u < PM_ITEMS; ++u)
+            if (s[u] >= 0 && s[u] < n) dst[at + u * TR_THREADS] = v[u];
+    }
 }
 
 rgs_status permute_launch(const rgs_gaussians* in, const int32_t* perm, const rgs_gaussians_grad* out, hipStream_t s) {
     if (in->n <= 0) return RGS_OK;
     const int rows = 11 + 3 * (in->sh_degree + 1) * (in->sh_degree + 1);
     const PermOut o{out->means, out->log_scales, out->quats, out->opacity, out->sh};
-    const int64_t per = TR_THREADS * PM_ITEMS;
-    hipLaunchKernelGGL(k_permute, dim3((unsigned)((in->n + per - 1) / per), (unsigned)rows), dim3(TR_THREADS), 0, s, *in,
-                       o, perm);
+    const int steps = in->n >= 8000000 ? 8 : 1;
+    const int64_t tile = (int64_t)steps * PM_STEP;
+    hipLaunchKernelGGL(k_permute, dim3((unsigned)((in->n + tile - 1) / tile), (unsigned)rows), dim3(TR_THREADS), 0, s, *in,
+                       o, rows, steps, perm);
     return launch_check();
 }
 
