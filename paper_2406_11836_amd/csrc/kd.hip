@@ -281,7 +281,12 @@ __global__ void k_kd_boxes(const float* __restrict__ split, int L, float* __rest
 // 16M Gaussians, 32 cells: 662 us with six comparisons per cell, three fp64
 // exponentials (the largest scale is that of the largest log scale) and
 // unconditional atomics; 189 now.
-static constexpr int KD_LEAF_BLOCKS = 2048;
+// A block ends with an atomic per (leaf, bound), which the other blocks' take turns
+// with: 1024 blocks (1M, 8 cells: 169 us for the partition, with 2048 196) but 2048
+// from 8M on, where the work counts (16M, 64 cells: 841 / 803).  With one leaf there
+// would be nothing but turns, in LDS and here: there a thread keeps its own bounds (1M
+// 115 -> 80 us, 16M sorted by coordinate 584 -> 178).
+static unsigned leaf_blocks(int64_t n) { return n < 8000000 ? 1024u : 2048u; }
 
 // The masks and cuts are scalar: the kernel is made for each depth.
 template <int L>
@@ -308,6 +313,8 @@ __global__ __launch_bounds__(KD_THREADS) void k_kd_leaves(int64_t n, const float
     __syncthreads();
     constexpr int Wm = (K + 31) / 32;
     const bool plain = s_plain != 0;
+    // one leaf: a thread keeps its own
+    uint32_t mn[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, mx[4] = {0u, 0u, 0u, 0u};
     for (int64_t i = (int64_t)blockIdx.x * KD_THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * KD_THREADS) {
         const float u[3] = {means[i], means[n + i], means[2 * n + i]};
         float ls = 0.f;
@@ -317,13 +324,19 @@ __global__ __launch_bounds__(KD_THREADS) void k_kd_leaves(int64_t n, const float
             const float c = d % 3 == 0 ? u[0] : (d % 3 == 1 ? u[1] : u[2]);
             leaf = 2 * leaf + (c < s_split[(1 << d) - 1 + leaf] ? 0 : 1);
         }
-        atomicAdd(&s_cnt[leaf], 1);
+        if (L > 0) atomicAdd(&s_cnt[leaf], 1);
         center_cell[i] = leaf;
         if (!own_mask && !bounds_key) continue;
         // D_i = d_factor * max scale; transcendental in fp64, rounded once
         const float smax = (float)exp((double)ls);
         const float Di = d_factor * smax;
-        if (bounds_key) {
+        if (L == 0) {
+            for (int a = 0; a < 3; ++a) {
+                mn[a] = min(mn[a], f2key(u[a]));
+                mx[a] = max(mx[a], f2key(u[a]));
+            }
+            mx[3] = max(mx[3], f2key(smax));
+        } else if (bounds_key) {
             for (int a = 0; a < 3; ++a) {
                 const uint32_t k = f2key(u[a]);
                 if (k < s_bk[a * K + leaf]) atomicMin(&s_bk[a * K + leaf], k);
@@ -361,6 +374,16 @@ __global__ __launch_bounds__(KD_THREADS) void k_kd_leaves(int64_t n, const float
         }
         own_mask[i * Wm] = (uint32_t)m;
         if (Wm > 1) own_mask[i * Wm + 1] = (uint32_t)((uint64_t)m >> 32);
+    }
+    if (L == 0) {
+        uint32_t r[7];
+        for (int a = 0; a < 3; ++a) r[a] = ~wave_max_u32(~mn[a]);
+        for (int a = 0; a < 4; ++a) r[3 + a] = wave_max_u32(mx[a]);
+        if ((threadIdx.x & 63) == 0) {
+            for (int a = 0; a < 3; ++a) atomicMin(&s_bk[a], r[a]);
+            for (int a = 3; a < 7; ++a) atomicMax(&s_bk[a], r[a]);
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) s_cnt[0] = (int32_t)n;
     }
     __syncthreads();
     for (int t = threadIdx.x; t < K; t += KD_THREADS)
@@ -451,7 +474,7 @@ rgs_status kd_partition(const rgs_gaussians* g, int L, float d_factor, int rule,
     }
     hipLaunchKernelGGL(k_kd_boxes, dim3(1), dim3(64), 0, s, kd->split, L, kd->box_lo, kd->box_hi, kd->counts);
     if (kd->cell_bounds) hipLaunchKernelGGL(k_kd_bounds_init, dim3(1), dim3(448), 0, s, bk, K);
-    const unsigned gridL = gridN < (unsigned)KD_LEAF_BLOCKS ? gridN : (unsigned)KD_LEAF_BLOCKS;
+    const unsigned gridL = gridN < leaf_blocks(n) ? gridN : leaf_blocks(n);
     if (n > 0) {
         using Leaves = decltype(&k_kd_leaves<0>);
         static const Leaves leaves[7] = {k_kd_leaves<0>, k_kd_leaves<1>, k_kd_leaves<2>, k_kd_leaves<3>,
