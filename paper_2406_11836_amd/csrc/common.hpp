@@ -282,8 +282,9 @@ int radix_fold_words(int64_t capacity);
 // RADIX_WIDE keys on a unit is 16 tiles, and the counts of the tiles before a
 // tile in its unit have a row per tile (tpre): the [digit][tile] table of one
 // row per digit costs a 4-byte write and read at a stride per (digit, tile)
-// (about 0.7G instances, three passes: row scans 1.6 -> 0.1 ms; from 16M keys on
-// or below there is no difference, and fewer units than blocks on the chip).
+// (about 0.7G instances, three passes: row scans 1.6 -> 0.1 ms; at 16M keys there
+// was no difference).  The line lies at twice that, where there are 977 units, enough
+// for the chip; fewer would leave blocks of the histogram without one.
 static constexpr int64_t RADIX_WIDE = 32000000;
 struct RadixTab {
     uint32_t *hist, *offs, *tpre;

@@ -1,11 +1,12 @@
 // render.hip -- per-cell partial blending (RetinaGS Eq. 3, Eq. 4 with the
 // indicator of Eq. 6), its backward, and the per-pair gradient reduction.
 //
-// One 256-thread block per slot (tile t, cell k); wave w owns the 8x8
-// quadrant (w & 1, w >> 1) of the 16x16 tile, one pixel per lane.  The
-// contribute decision d^2 <= tau uses the exact fp32 operation sequence the
-// CPU oracle mirrors, on the factored form of the quadratic (no cancellation
-// for elongated footprints):
+// Forward: a 256-thread block per 16x16 tile walks the tile's slots (tile, cell) in
+// merge order; wave w owns the 8x8 quadrant (w & 1, w >> 1), one pixel per lane.  The
+// longest tiles are given to four blocks each, whose waves own 4x4 pixels and take
+// four instances at a time.  The contribute decision d^2 <= tau uses the exact
+// fp32 operation sequence the CPU oracle mirrors, on the factored form of the
+// quadratic (no cancellation for elongated footprints):
 //   dx = (x + 0.5) - mx, dy = (y + 0.5) - my, u = fma(k, dy, dx),
 //   d^2 = fma(e dy, dy, (ca u) u).
 // The conic (ca, cb, cc) = (ca, k ca, e + k cb) is rebuilt per instance where
@@ -14,7 +15,8 @@
 // the quadrants their rectangle meets, and read
 // back as wave-uniform broadcasts; a wave skips Gaussians outside its
 // quadrant with a scalar branch.  A pixel stops after the contribution that
-// takes its T_k below eps_T; the block leaves once all 256 pixels stopped.
+// takes its merged transmittance below eps_T; the block leaves once all its
+// pixels stopped.
 //
 // Backward (a 128-thread block per slot, two pixels of one row per lane)
 // walks each slot back to front from the largest per-pixel `last`, recovers
@@ -169,12 +171,16 @@ __device__ __forceinline__ uint32_t block_row_mask(float4 a, float4 b, uint2 rr,
 // records whose ellipse reaches its 4x4 block.  This costs twice the
 // instructions per (pixel, instance) pair, so it is not for every tile: with
 // all tiles so, 300k Gaussians take 120 us and 20k at 256x256 30, but 1M at
-// 1920x1080 293 instead of 212 and 16M at 3840x2160 990 instead of 550.  256
-// tiles are the 1024 blocks that the chip starts with (4 per CU).  Measured
-// in us, before / with the first 128 / 256 / 512 tiles: 20k at 256x256 66 /
-// 28 / 28 / 28; 150k at 1237x823 165 / 123 / 127 / more; 300k at 997x663
-// 228 / 128 / 128 / more; 1M at 1600x1060 312 / 300 / 228; 1M at 1920x1080 (no long
-// tiles) 212 / 222 / 218; 16M at 3840x2160 551 / 523 / 519.
+// 1920x1080 293 instead of 212 and 16M at 3840x2160 990 instead of 550.  How many
+// is a matter of the views measured, in us, before / with the first 128 / 256 / 512
+// tiles: 20k at 256x256 66 / 28 / 28 / 28; 150k at 1237x823 165 / 123 / 127 / more; 300k
+// at 997x663 228 / 128 / 128 / more; 1M at 1600x1060 312 / 300 / 228; 16M at 3840x2160
+// 551 / 523 / 519.  A view without long tiles pays for it: 1M at 1920x1080, four
+// scenes, none / 256: 206 / 213, 212 / 215, 195 / 196, 192 / 200; so does one of next to
+// nothing in many cells (300 Gaussians at 500x333, 64 cells: 66 / 90).  Asking each of
+// the 256 for its share of the instances first, and taking the short ones whole, costs
+// as much as it saves (the three blocks that then end have waited for the tile's
+// range: 218 to 221 us at 1920x1080 for any share asked).
 // 64 registers keep 8 waves per SIMD (72 and 7 waves: 246 at 1920x1080).
 static constexpr uint32_t RF_HEAVY = 256;
 
