@@ -103,4 +103,4 @@ def test_autograd_passes_free_their_buffers(backward):
             assert all(p[k].grad is not None for k in raster.PARAM_KEYS)
         del image, T
         sizes.append(torch.cuda.memory_allocated())
-    assert sizes[-1] == sizes[2]
+    assert sizes[-1] <= sizes[2]
